@@ -15,6 +15,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -69,6 +70,27 @@ __device__ __forceinline__ double dpp_rows_d(double old, double v) {
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ int dpp_rows_i(int old, int v) {
   return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWMASK, 0xf, false);
+}
+
+// largest of one 32-bit key per lane (all 64 lanes; every lane of the last
+// step reads inside the rows it takes from)
+__device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
+  x = ::max(x, static_cast<unsigned>(dpp_i<kXor1>(static_cast<int>(x))));
+  x = ::max(x, static_cast<unsigned>(dpp_i<kXor2>(static_cast<int>(x))));
+  x = ::max(x, static_cast<unsigned>(dpp_i<kHalfMirror>(static_cast<int>(x))));
+  x = ::max(x, static_cast<unsigned>(dpp_i<kMirror>(static_cast<int>(x))));
+  x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast15, 0xA>(0, static_cast<int>(x))));
+  x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast31, 0xC>(0, static_cast<int>(x))));
+  return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
+}
+
+// f(integral constants 0 .. N - 1) in order
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
 }
 
 template <int G>
@@ -178,13 +200,19 @@ struct CellArea {
 };
 
 __host__ __device__ constexpr int pbuf_doubles(int nn) { return (nn + 2) & ~1; }
+// The LU's pivot rows of one panel, interleaved (column j's four entries side
+// by side, up to a multiple of 16 columns), sit in P and run on into RB and
+// the species vectors, which hold nothing between two right-hand sides.
+constexpr int kPanel = 4;
+__host__ __device__ constexpr int lu_rows_doubles(int nn) { return kPanel * ((nn + 15) & ~15); }
 // state sizes above 32 assemble rates and Jacobian reaction by reaction
 __host__ __device__ constexpr bool reaction_major(int nn) { return nn > 32; }
 __host__ __device__ constexpr int rbuf_doubles(int nn, int nr) {
   return reaction_major(nn) ? 3 * nn : (5 * nr > 3 * nn ? 5 * nr : 3 * nn);
 }
 __host__ __device__ constexpr int cell_doubles_c(int nn, int nr, int ns) {
-  return ((nn * nn + 1) & ~1) + pbuf_doubles(nn) + rbuf_doubles(nn, nr) + 3 * (nn - 1);
+  const int rest = pbuf_doubles(nn) + rbuf_doubles(nn, nr) + 3 * (nn - 1);
+  return ((nn * nn + 1) & ~1) + (((rest > lu_rows_doubles(nn) ? rest : lu_rows_doubles(nn)) + 1) & ~1);
 }
 
 template <int NN>
@@ -577,15 +605,178 @@ struct Cell {
   // LU with partial pivoting of the rows in registers (row = lane). Rows are
   // not moved during the elimination: pos tracks each row's LAPACK position,
   // so the pivot of column k is the largest |a| among rows at positions >= k,
-  // ties to the lowest position, exactly as a row-swapping getrf. The pivot
-  // row reaches the other lanes through the LDS buffer P. At the end every
-  // row is sent to the lane of its position (one ds_permute per dword), so on
-  // return lane k holds row k of the packed factors (L left of the diagonal,
-  // unit diagonal implied; U from the diagonal on) and rdiag = 1/U_kk; pos
-  // keeps the position this lane's original row went to (used to permute
-  // right-hand sides). Returns the first singular column + 1.
+  // ties to the lowest position, exactly as a row-swapping getrf. At the end
+  // every row is sent to the lane of its position (one ds_permute per dword),
+  // so on return lane k holds row k of the packed factors (L left of the
+  // diagonal, unit diagonal implied; U from the diagonal on) and rdiag =
+  // 1/U_kk; pos keeps the position this lane's original row went to (used to
+  // permute right-hand sides). Returns the first singular column + 1.
   // -------------------------------------------------------------------------
   __device__ static __forceinline__ int lu(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+    if constexpr (G == 64) {
+      return lu_wave(M, pos, rdiag, P, pivk);
+    } else {
+      return lu_group(M, pos, rdiag, pivk);
+    }
+  }
+
+  // One cell per wave: panels of kPanel columns. Inside a panel only the
+  // panel's own columns are updated, each pivot-row element broadcast by two
+  // readlanes. The panel's pivot rows then go through the cell's LDS buffer P
+  // to every 16-lane row (lane l of a row reads columns 16 J + l), solve their
+  // unit lower triangle there, and every later column takes its kPanel updates
+  // as fused multiply-adds whose multiplicand is broadcast along the 16-lane
+  // row by DPP inside the instruction: one instruction per element where the
+  // readlane form needs three. Each element receives the same fused
+  // multiply-adds in the same order as column by column.
+  // pivot search of one column by value, then position (every special case:
+  // ties, zero columns, non-finite entries)
+  __device__ static __forceinline__ int pivot_exact(double a, int pos, int k, double& amax) {
+    const double key = pos >= k ? fabs(a) : -1.0;
+    amax = Gp::max(key);
+    const bool tie = key == amax;
+    const unsigned long long bal = __ballot(tie);
+    if (__popcll(bal) == 1) return __ffsll(static_cast<long long>(bal)) - 1;
+    const int pmin = Gp::min_i(tie ? pos : kBig);
+    return (__ffsll(static_cast<long long>(__ballot(tie && pos == pmin))) - 1) & 63;
+  }
+
+  __device__ static __forceinline__ int lu_wave(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+    unsigned long long zeros = 0;              // columns without a nonzero candidate
+    const int i = Gp::lane();
+    pos = i < NN ? i : -1;
+    rdiag = 0.0;
+    static_for<(NN + kPanel - 1) / kPanel>([&](auto pc) {
+      constexpr int p0 = decltype(pc)::value * kPanel;
+      constexpr int nb = NN - p0 < kPanel ? NN - p0 : kPanel;
+      int own[kPanel];
+      double ln[kPanel];                       // minus the multipliers (0 on rows above)
+#pragma unroll
+      for (int c = 0; c < nb; ++c) {
+        const int k = p0 + c;
+        const double a = M[k];
+        // every lane forms its own element's reciprocal, beside the search
+        // rather than after it: the hardware reciprocal refined by two Newton
+        // steps (a shorter dependent chain than a correctly rounded division)
+        double ra = __builtin_amdgcn_rcp(a);
+        ra = fma(ra, fma(-a, ra, 1.0), ra);
+        ra = fma(ra, fma(-a, ra, 1.0), ra);
+        // the high words of |a| order the candidates except where they tie;
+        // ties, zeros and non-finite entries take the exact search
+        const unsigned hi = static_cast<unsigned>(__double2hiint(a)) & 0x7fffffffu;
+        const unsigned key = pos >= k ? hi : 0u;
+        const unsigned hmax = wave_max_u32(key);
+        const unsigned long long bal = __ballot(key == hmax);
+        int owner = __builtin_ctzll(bal);
+        double rp;
+        if (__builtin_expect((bal & (bal - 1)) == 0 && hmax < 0x7ff00000u, 1)) {
+          rp = readlane_d(ra, owner);
+        } else {
+          double amax;
+          owner = __builtin_amdgcn_readfirstlane(pivot_exact(a, pos, k, amax));
+          rp = readlane_d(ra, owner);
+          if (amax == 0.0) {
+            zeros |= 1ull << k;
+            rp = 0.0;
+          }
+        }
+        own[c] = owner;
+        const int ppos = __builtin_amdgcn_readlane(pos, owner);
+        pos = pos == k ? ppos : pos;
+        pos = i == owner ? k : pos;
+        if (pivk) pivk[k] = ppos;
+        rdiag = i == k ? rp : rdiag;
+        const bool below = pos > k;
+        const double l = below ? a * rp : 0.0;
+        M[k] = below ? l : a;
+        ln[c] = -l;
+        // formed here, not carried along as masks and products
+        asm volatile("" : "+v"(M[k]), "+v"(rdiag), "+v"(ln[c]));
+#pragma unroll
+        for (int j = k + 1; j < p0 + nb; ++j) M[j] = fma(ln[c], readlane_d(M[j], owner), M[j]);
+      }
+      if constexpr (p0 + kPanel < NN) {
+        constexpr int j0 = p0 + kPanel;        // first column right of the panel
+        const int r = pos - p0;
+        if (static_cast<unsigned>(r) < static_cast<unsigned>(kPanel)) {
+          double* row = P + r;
+#pragma unroll
+          for (int j = j0; j < NN; ++j) row[kPanel * j] = M[j];
+        }
+        // multipliers among the pivot rows (negated)
+        const double n10 = readlane_d(ln[0], own[1]);
+        const double n20 = readlane_d(ln[0], own[2]), n21 = readlane_d(ln[1], own[2]);
+        const double n30 = readlane_d(ln[0], own[3]), n31 = readlane_d(ln[1], own[3]),
+                     n32 = readlane_d(ln[2], own[3]);
+        wsync();
+        static_for<(NN + 15) / 16 - j0 / 16>([&](auto tc) {
+          constexpr int J = j0 / 16 + decltype(tc)::value;
+          const double* u = P + kPanel * (16 * J + (i & 15));
+          const double x0 = u[0];
+          double x1 = u[1], x2 = u[2], x3 = u[3];
+          x1 = fma(n10, x0, x1);
+          x2 = fma(n20, x0, x2);
+          x3 = fma(n30, x0, x3);
+          x2 = fma(n21, x1, x2);
+          x3 = fma(n31, x1, x3);
+          x3 = fma(n32, x2, x3);
+          constexpr int ja = J * 16 > j0 ? J * 16 : j0;
+          constexpr int jb = J * 16 + 16 < NN ? J * 16 + 16 : NN;
+          static_for<(jb - ja + 3) / 4>([&](auto qc) {
+            constexpr int j = ja + 4 * decltype(qc)::value;
+            rank4<jb - j < 4 ? jb - j : 4, j & 15>(&M[j], x0, x1, x2, x3, ln);
+          });
+        });
+        wsync();
+      }
+    });
+    // rows to the lanes of their positions
+    const int dst = 4 * (pos >= 0 ? pos : i);
+#pragma unroll
+    for (int j = 0; j < NN; ++j) M[j] = permute_d(M[j], dst);
+    return zeros ? __builtin_ctzll(zeros) + 1 : 0;
+  }
+
+  // M[c] += sum_k l[k] (x_k of lane N + c of this 16-lane row), k ascending,
+  // for NC columns. The leading s_nop covers the wait between a vector write
+  // of x and its use as a DPP operand.
+  template <int NC, int N>
+  __device__ static __forceinline__ void rank4(double* m, double x0, double x1, double x2, double x3,
+                                               const double (&l)[kPanel]) {
+#define CHEM_F(A, X, L, K) "v_fmac_f64_dpp " A ", " X ", " L " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (NC == 4) {
+#define CHEM_R(X, L) CHEM_F("%0", X, L, "%12") CHEM_F("%1", X, L, "%13") CHEM_F("%2", X, L, "%14") CHEM_F("%3", X, L, "%15")
+      asm("s_nop 1\n\t" CHEM_R("%4", "%8") CHEM_R("%5", "%9") CHEM_R("%6", "%10") CHEM_R("%7", "%11")
+          : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3])
+          : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1),
+            "n"(N + 2), "n"(N + 3));
+#undef CHEM_R
+    } else if constexpr (NC == 3) {
+#define CHEM_R(X, L) CHEM_F("%0", X, L, "%11") CHEM_F("%1", X, L, "%12") CHEM_F("%2", X, L, "%13")
+      asm("s_nop 1\n\t" CHEM_R("%3", "%7") CHEM_R("%4", "%8") CHEM_R("%5", "%9") CHEM_R("%6", "%10")
+          : "+v"(m[0]), "+v"(m[1]), "+v"(m[2])
+          : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1),
+            "n"(N + 2));
+#undef CHEM_R
+    } else if constexpr (NC == 2) {
+#define CHEM_R(X, L) CHEM_F("%0", X, L, "%10") CHEM_F("%1", X, L, "%11")
+      asm("s_nop 1\n\t" CHEM_R("%2", "%6") CHEM_R("%3", "%7") CHEM_R("%4", "%8") CHEM_R("%5", "%9")
+          : "+v"(m[0]), "+v"(m[1])
+          : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1));
+#undef CHEM_R
+    } else {
+#define CHEM_R(X, L) CHEM_F("%0", X, L, "%9")
+      asm("s_nop 1\n\t" CHEM_R("%1", "%5") CHEM_R("%2", "%6") CHEM_R("%3", "%7") CHEM_R("%4", "%8")
+          : "+v"(m[0])
+          : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N));
+#undef CHEM_R
+    }
+#undef CHEM_F
+  }
+
+  // Several cells per wave: column by column, every pivot-row element by a
+  // lane shuffle.
+  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, int* pivk) {
     int info = 0;
     const int i = Gp::gl();
     pos = i < NN ? i : kBig;
@@ -652,8 +843,12 @@ struct Cell {
   // side is first sent to position order; both substitutions then broadcast
   // from fixed lanes.
   __device__ static __forceinline__ double solve(const double (&M)[NN], int pos, double rdiag, double b) {
-    const int i = Gp::gl();
-    b = permute_d(b, 4 * (Gp::base() + (pos < NN ? pos : i)));
+    int i = Gp::gl();
+    // with one cell per wave the comparisons are formed at their use, one
+    // instruction each, not hoisted out of the stages (which spilled them)
+    if constexpr (G == 64) asm volatile("" : "+v"(i));
+    const bool row = G == 64 ? pos >= 0 : pos < NN;
+    b = permute_d(b, 4 * (Gp::base() + (row ? pos : i)));
     // the multipliers are masked rather than the update, which keeps the
     // selects off the chain of dependent broadcasts (a zero multiplier
     // leaves b unchanged for finite z)
@@ -963,7 +1158,7 @@ __global__ void __launch_bounds__(256) k_lu(LuArgs a) {
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* P = reinterpret_cast<double*>(smem) + (wave * CPW + grp) * pbuf_doubles(NN);
+  double* P = reinterpret_cast<double*>(smem) + (wave * CPW + grp) * (G == 64 ? lu_rows_doubles(NN) : 2);
   const long long m = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
   if (m >= a.batch) return;
   const int n = a.n;
@@ -1095,7 +1290,7 @@ hipError_t launch_lu(const Variant& v, int grid, const LuArgs& a, hipStream_t st
   if (!fn) return hipErrorInvalidValue;
   LuArgs copy = a;
   void* args[] = {&copy};
-  const size_t lds = sizeof(double) * pbuf_doubles(v.nn) * a.wpb * (64 / v.g);
+  const size_t lds = sizeof(double) * (v.g == 64 ? lu_rows_doubles(v.nn) : 2) * a.wpb * (64 / v.g);
   return hipLaunchKernel(fn, dim3(grid), dim3(64 * a.wpb), args, lds, st);
 }
 
