@@ -383,17 +383,33 @@ struct Shape {
   chemk::Variant v;
   int wpb = 4;
   int cpw = 1;
-  size_t lds = 0;
+  size_t lds = 0;          // bytes per block of the integration kernel
+  size_t lds_own = 0;      // the same with a Jacobian buffer per cell (evaluation kernel)
+  bool share_j = false;
 };
 
-int pick_shape(const chem_solver* s, const chem_opts& o, Shape& sh) {
+// Waves per block when the caller leaves them open. Where waves can share
+// Jacobian buffers (two blocks of four to a CU):
+// - up to 8 cells per CU, one wave each with a buffer of its own: the longest
+//   cell's chain of steps sets the time and sharing only delays it (54
+//   species, 131 cells: 18.4 against 19.5 ms, 2048 cells: 25.6 against 26.0);
+// - the static map, two: a block ends with its longest cell (16411 cells: 93
+//   ms with two, 101 with one, 123 with four).
+int auto_wpb(const chem_solver* s, const chem_opts& o, int64_t n, const chemk::Variant& v) {
+  if (n < 1 || !chemk::share_j(v, s->nr, s->ns, s->margs.lds_bytes, 4, kMaxLds)) return 4;
+  if (n <= 8LL * s->cus) return 1;
+  return o.schedule == CHEM_PLAIN ? 2 : 4;
+}
+
+// n: cells of the launch (0: not an integration)
+int pick_shape(const chem_solver* s, const chem_opts& o, int64_t n, Shape& sh) {
   if (s->wide) {
     if (o.cells_per_wave > 1)
       return fail(CHEM_EUNSUPPORTED, "state size " + std::to_string(s->n) + " runs one cell per workgroup");
     sh.v = s->variants[0];
     sh.cpw = 1;
     sh.wpb = chemk::kWideThreads / 64;
-    sh.lds = s->wide_lds;
+    sh.lds = sh.lds_own = s->wide_lds;
     return CHEM_OK;
   }
   // variant by requested cells per wave, else the first compiled one
@@ -411,13 +427,14 @@ int pick_shape(const chem_solver* s, const chem_opts& o, Shape& sh) {
                                          " not compiled for state size " + std::to_string(s->n));
   }
   sh.cpw = 64 / sh.v.g;
-  const size_t cell_bytes = sizeof(double) * chemk::cell_doubles(sh.v.nn, s->nr, s->ns);
-  const size_t blob = s->margs.lds_bytes;
-  int wpb = o.waves_per_block > 0 ? o.waves_per_block : 4;
-  while (wpb > 1 && blob + wpb * sh.cpw * cell_bytes > kMaxLds) --wpb;
-  sh.lds = blob + wpb * sh.cpw * cell_bytes;
-  if (sh.lds > kMaxLds)
+  const int blob = s->margs.lds_bytes;
+  int wpb = o.waves_per_block > 0 ? o.waves_per_block : auto_wpb(s, o, n, sh.v);
+  while (wpb > 1 && chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, false) > kMaxLds) --wpb;
+  sh.lds_own = chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, false);
+  if (sh.lds_own > kMaxLds)
     return fail(CHEM_EUNSUPPORTED, "mechanism and one cell's work area exceed the 160 KB LDS");
+  sh.share_j = chemk::share_j(sh.v, s->nr, s->ns, blob, wpb, kMaxLds);
+  sh.lds = sh.share_j ? chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, true) : sh.lds_own;
   sh.wpb = wpb;
   return CHEM_OK;
 }
@@ -483,7 +500,7 @@ int launch_step(chem_solver* s, const chem_opts& o, int64_t n, double dt, const 
                 double* h_io, int32_t* n_acc, int32_t* n_rej, int8_t* status, int accumulate,
                 const int* perm, hipStream_t st, bool head_set = false, const StaticRes* res = nullptr) {
   Shape sh;
-  if (int rc = pick_shape(s, o, sh)) return rc;
+  if (int rc = pick_shape(s, o, n, sh)) return rc;
   chemk::IntegrateArgs a{};
   a.m = s->margs;
   a.o.rtol = o.rtol;
@@ -505,6 +522,7 @@ int launch_step(chem_solver* s, const chem_opts& o, int64_t n, double dt, const 
   a.n_fev = s->d_nfev;
   a.accumulate = accumulate;
   a.cell_doubles = chemk::cell_doubles(sh.v.nn, s->nr, s->ns);
+  a.share_j = sh.share_j ? 1 : 0;
   a.wpb = sh.wpb;
   a.perm = perm;
   unsigned long long* const head = res ? res->head : s->d_head;
@@ -731,7 +749,7 @@ int chem_eval_rhs_jac(chem_solver* s, int64_t n, const double* phi, double* f, d
   DeviceGuard g(s->dev);
   chem_opts o = s->opts;
   Shape sh;
-  if (int rc = pick_shape(s, o, sh)) return rc;
+  if (int rc = pick_shape(s, o, 0, sh)) return rc;
   chemk::EvalArgs a{};
   a.m = s->margs;
   a.n = n;
@@ -751,7 +769,7 @@ int chem_eval_rhs_jac(chem_solver* s, int64_t n, const double* phi, double* f, d
   a.cell_doubles = chemk::cell_doubles(sh.v.nn, s->nr, s->ns);
   const long long per_block = static_cast<long long>(sh.wpb) * sh.cpw;
   const long long grid = (n + per_block - 1) / per_block;
-  HIP_TRY(chemk::launch_eval(sh.v, static_cast<int>(grid), a, sh.lds, static_cast<hipStream_t>(stream)), "eval launch");
+  HIP_TRY(chemk::launch_eval(sh.v, static_cast<int>(grid), a, sh.lds_own, static_cast<hipStream_t>(stream)), "eval launch");
   return CHEM_OK;
 }
 
@@ -760,7 +778,7 @@ int chem_lu_batch(chem_solver* s, int64_t batch, double* A, int32_t* piv, int32_
   if (batch == 0) return CHEM_OK;
   DeviceGuard g(s->dev);
   Shape sh;
-  if (int rc = pick_shape(s, s->opts, sh)) return rc;
+  if (int rc = pick_shape(s, s->opts, 0, sh)) return rc;
   chemk::LuArgs a{};
   a.batch = batch;
   a.n = s->n;
@@ -970,7 +988,7 @@ static int tune(chem_solver* s, int64_t n_sample, const double* phi, double dt, 
         o.waves_per_block = wpb;
         o.queue_chunk = chunks[ci];
         Shape sh;
-        if (pick_shape(s, o, sh) != CHEM_OK || sh.wpb != wpb) continue;
+        if (pick_shape(s, o, 0, sh) != CHEM_OK || sh.wpb != wpb) continue;
         float ms = 0;
         for (int rep = 0; rep < 2; ++rep) {   // first repetition warms up
           if (hipMemsetAsync(h, 0, n_sample * sizeof(double), st) != hipSuccess ||
@@ -1057,7 +1075,7 @@ int chem_autotune_cached(chem_solver* s, const char* cache_path, int64_t n_sampl
       t.waves_per_block = static_cast<int32_t>(wpb);
       t.queue_chunk = static_cast<int32_t>(chunk);
       Shape sh;
-      if (chunk < 1 || chunk > 1 << 20 || pick_shape(s, t, sh) != CHEM_OK) continue;
+      if (chunk < 1 || chunk > 1 << 20 || pick_shape(s, t, 0, sh) != CHEM_OK) continue;
       o = t;   // the last valid line for the key wins
       hit = true;
     }

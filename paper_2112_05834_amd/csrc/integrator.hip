@@ -182,14 +182,16 @@ struct Grp {
   }
 };
 
-// Per-cell LDS area layout (doubles): J [NN*NN] row-major, pivot-row buffer
-// P [NN+1 rounded to even], a reaction/species buffer RB, then the
-// per-species vectors C, gRT, hRT [NN-1 each; entries from ns on are zero,
-// so column loops run to NN-1 without a bound check]. RB holds, for state
-// sizes up to 32, the per-reaction rate of progress (and with the Jacobian
-// kf*theta, kr*theta, q0*dtheta/d[M], dq/dT) read by the species pass
-// [max(5*nr, 3*NN)]; above 32 only the species sums omega, d omega/dT and
-// sum nu q0 dtheta/d[M] [3*NN] that the reaction lanes add into.
+// A block's LDS after the mechanism image: one Jacobian J [NN*NN] row-major
+// per cell, or per pair of waves that take turns with it (below), then every
+// cell's own area: the pivot-row buffer P [NN+1 rounded to even], a
+// reaction/species buffer RB, then the per-species vectors C, gRT, hRT [NN-1
+// each; entries from ns on are zero, so column loops run to NN-1 without a
+// bound check]. RB holds, for state sizes up to 32, the per-reaction rate of
+// progress (and with the Jacobian kf*theta, kr*theta, q0*dtheta/d[M], dq/dT)
+// read by the species pass [max(5*nr, 3*NN)]; above 32 only the species sums
+// omega, d omega/dT and sum nu q0 dtheta/d[M] [3*NN] that the reaction lanes
+// add into.
 struct CellArea {
   double* J;
   double* P;
@@ -212,14 +214,18 @@ __host__ __device__ constexpr int rbuf_doubles(int nn, int nr) {
 }
 __host__ __device__ constexpr int cell_doubles_c(int nn, int nr, int ns) {
   const int rest = pbuf_doubles(nn) + rbuf_doubles(nn, nr) + 3 * (nn - 1);
-  return ((nn * nn + 1) & ~1) + (((rest > lu_rows_doubles(nn) ? rest : lu_rows_doubles(nn)) + 1) & ~1);
+  return ((rest > lu_rows_doubles(nn) ? rest : lu_rows_doubles(nn)) + 1) & ~1;
 }
+__host__ __device__ constexpr int j_doubles_c(int nn) { return (nn * nn + 1) & ~1; }
+// Sizes whose waves may share a Jacobian buffer in pairs: one cell per wave,
+// and two blocks of four waves, each with two buffers, fit the LDS of a CU.
+__host__ __device__ constexpr bool can_share_j(int nn) { return nn > 32 && nn <= 55; }
 
 template <int NN>
-__device__ __forceinline__ CellArea cell_area(double* base, int nr, int ns) {
+__device__ __forceinline__ CellArea cell_area(double* J, double* base, int nr) {
   CellArea c;
-  c.J = base;
-  c.P = base + ((NN * NN + 1) & ~1);
+  c.J = J;
+  c.P = base;
   c.RB = c.P + pbuf_doubles(NN);
   c.C = c.RB + rbuf_doubles(NN, nr);
   c.gRT = c.C + (NN - 1);
@@ -308,6 +314,31 @@ __device__ __forceinline__ void rx_scatter(const MechLds& L, const double* C, co
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// the Jacobian buffer that two waves of a block share
+// ---------------------------------------------------------------------------
+// A wave needs the buffer only from the start of a Jacobian's assembly until
+// M = g I - J is in its registers, well under half of an attempted step, so
+// two waves take turns with one. That halves the largest part of a cell's LDS
+// and lets two waves run on every SIMD. The lock is a word of LDS (NULL: the
+// buffer is the wave's own); a holder never waits for anything while it holds
+// it, and gives it back on every path, so each wait ends.
+__device__ __forceinline__ void j_acquire(int* lock) {
+  if (!lock) return;
+  for (;;) {
+    int held = 0;
+    if (__lane_id() == 0) held = __hip_atomic_exchange(lock, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_amdgcn_readfirstlane(held) == 0) break;
+    __builtin_amdgcn_s_sleep(8);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+__device__ __forceinline__ void j_release(int* lock) {
+  if (!lock) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if (__lane_id() == 0) __hip_atomic_store(lock, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,8 +907,8 @@ struct Cell {
   // the kernels of the default options carry none of their code.
   template <int SCHEME, bool GEN>
   __device__ static __forceinline__ void integrate(const MechArgs& A, const MechLds& L, const CellArea& ca,
-                                                   const OptsDev& o, double p, double dt, double& y,
-                                                   double& hio, int& nacc_o, int& nrej_o, int& status_o,
+                                                   int* jlock, const OptsDev& o, double p, double dt,
+                                                   double& y, double& hio, int& nacc_o, int& nrej_o, int& status_o,
                                                    int& njac_o, int& nfev_o) {
     using TB = Tab<SCHEME>;
     const int ns = A.ns;
@@ -904,14 +935,6 @@ struct Cell {
         break;
       }
       if (need) {
-        if (GEN && o.jac_fd) {
-          f0 = rhs<false>(A, L, ca, p, y);
-          fd_jacobian(A, L, ca, p, y, f0, nb);
-        } else {
-          f0 = rhs<true>(A, L, ca, p, y);
-          if (nb) reduce_bath(ca, ns);
-        }
-        need = false;
         ++njac;
         nfev += (GEN && o.jac_fd) ? 1 + n : 1;
       }
@@ -926,6 +949,20 @@ struct Cell {
         status = 2;
         break;
       }
+      // f and J of the step start. A buffer of the wave's own keeps J across
+      // rejected attempts; a shared one may have been overwritten, and the
+      // same J is formed again (a few per cent of the attempts).
+      j_acquire(jlock);
+      if (need || jlock) {
+        if (GEN && o.jac_fd) {
+          f0 = rhs<false>(A, L, ca, p, y);
+          fd_jacobian(A, L, ca, p, y, f0, nb);
+        } else {
+          f0 = rhs<true>(A, L, ca, p, y);
+          if (nb) reduce_bath(ca, ns);
+        }
+        need = false;
+      }
       const double g = 1.0 / (TB::gamma * hc);
       if (i < NN) {
 #pragma unroll
@@ -934,6 +971,7 @@ struct Cell {
 #pragma unroll
         for (int j = 0; j < NN; ++j) M[j] = 0.0;
       }
+      j_release(jlock);
       const int info = lu(M, pos, rdiag, ca.P, nullptr);
       ++att;
       if (info) {
@@ -1042,7 +1080,7 @@ __device__ __forceinline__ void cell_features(int ns, double y, double p, double
 // kernels
 // ---------------------------------------------------------------------------
 template <int NN, int G, int SCHEME, bool GEN>
-__device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& L, const CellArea& ca,
+__device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& L, const CellArea& ca, int* jlock,
                                          long long cell) {
   using C = Cell<NN, G>;
   const int ns = a.m.ns;
@@ -1055,7 +1093,7 @@ __device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& 
   if (a.log.cap > 0) cell_features<G>(ns, y, p, a.dt, ft);
   double h = a.h_io ? a.h_io[cell] : 0.0;
   int nacc, nrej, st, njac, nfev;
-  C::template integrate<SCHEME, GEN>(a.m, L, ca, a.o, p, a.dt, y, h, nacc, nrej, st, njac, nfev);
+  C::template integrate<SCHEME, GEN>(a.m, L, ca, jlock, a.o, p, a.dt, y, h, nacc, nrej, st, njac, nfev);
   double* pout = a.phi_out + cell * w2;
   if (i == 0) {
     pout[0] = y;
@@ -1089,26 +1127,36 @@ __device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& 
   }
 }
 
-// Large state sizes run one wave per SIMD (the per-cell LDS area allows no
-// more), so let the register allocator use the whole 512-entry budget.
+// Waves per SIMD that the register allocator plans for: two where pairs of
+// waves share a Jacobian buffer and two blocks fit a CU's LDS (256 registers
+// a lane), one for the other large state sizes.
 template <int NN>
-constexpr int max_waves_per_eu() { return NN >= 32 ? 1 : 2; }
+constexpr int min_waves_per_eu() { return can_share_j(NN) ? 2 : 1; }
+template <int NN>
+constexpr int max_waves_per_eu() { return NN >= 32 && !can_share_j(NN) ? 1 : 2; }
 
 template <int NN, int G, bool PERSIST, int SCHEME, bool GEN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, max_waves_per_eu<NN>())))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<NN>(), max_waves_per_eu<NN>())))
 k_integrate(IntegrateArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  stage_mech(smem, a.m);
-  const MechLds L = mech_views(smem, a.m);
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* base = reinterpret_cast<double*>(smem + a.m.lds_bytes) +
-                 static_cast<long long>(wave * CPW + grp) * a.cell_doubles;
-  const CellArea ca = cell_area<NN>(base, a.m.nr, a.m.ns);
+  double* const work = reinterpret_cast<double*>(smem + a.m.lds_bytes);
+  const int nj = can_share_j(NN) && a.share_j ? (a.wpb + 1) / 2 : a.wpb * CPW;     // Jacobian buffers
+  const int jb = can_share_j(NN) && a.share_j ? wave / 2 : wave * CPW + grp;
+  double* const cells = work + nj * j_doubles_c(NN);
+  int* jlock = nullptr;
+  if (can_share_j(NN) && a.share_j) {
+    jlock = reinterpret_cast<int*>(cells + a.wpb * a.cell_doubles) + jb;
+    if (threadIdx.x % 128 == 0) *jlock = 0;
+  }
+  stage_mech(smem, a.m);        // ends in a barrier
+  const MechLds L = mech_views(smem, a.m);
+  const CellArea ca = cell_area<NN>(work + jb * j_doubles_c(NN), cells + (wave * CPW + grp) * a.cell_doubles, a.m.nr);
   if (!PERSIST) {
     const long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
-    if (cell < a.n) run_cell<NN, G, SCHEME, GEN>(a, L, ca, cell);
+    if (cell < a.n) run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, cell);
   } else {
     for (;;) {
       unsigned long long idx = 0;
@@ -1118,7 +1166,7 @@ k_integrate(IntegrateArgs a) {
       const long long end = min(static_cast<long long>(idx) + a.chunk, a.n);
       for (long long q = static_cast<long long>(idx); q < end; ++q) {
         const long long cell = a.perm ? static_cast<long long>(a.perm[q]) : q;
-        run_cell<NN, G, SCHEME, GEN>(a, L, ca, cell);
+        run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, cell);
       }
     }
   }
@@ -1133,9 +1181,10 @@ __global__ void __launch_bounds__(256) k_eval(EvalArgs a) {
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* base = reinterpret_cast<double*>(smem + a.m.lds_bytes) +
-                 static_cast<long long>(wave * CPW + grp) * a.cell_doubles;
-  const CellArea ca = cell_area<NN>(base, a.m.nr, a.m.ns);
+  double* const work = reinterpret_cast<double*>(smem + a.m.lds_bytes);
+  const int own = wave * CPW + grp;
+  const CellArea ca = cell_area<NN>(work + own * j_doubles_c(NN),
+                                    work + a.wpb * CPW * j_doubles_c(NN) + own * a.cell_doubles, a.m.nr);
   const long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
   if (cell >= a.n) return;
   const int ns = a.m.ns, n = ns + 1;
@@ -1226,6 +1275,19 @@ int variants_for(int n, Variant* out, int max_out) {
 }
 
 int cell_doubles(int nn, int nr, int ns) { return cell_doubles_c(nn, nr, ns); }
+
+size_t block_lds(const Variant& v, int nr, int ns, int mech_bytes, int wpb, bool share_j) {
+  const int cpw = 64 / v.g;
+  const size_t nj = share_j ? (wpb + 1) / 2 : wpb * cpw;
+  return mech_bytes + sizeof(double) * (nj * j_doubles_c(v.nn) + static_cast<size_t>(wpb) * cpw * cell_doubles_c(v.nn, nr, ns)) +
+         (share_j ? 16 : 0);
+}
+
+bool share_j(const Variant& v, int nr, int ns, int mech_bytes, int wpb, size_t lds_per_cu) {
+  // pays only where it brings a second block to the CU; one wave has none to
+  // share with
+  return v.g == 64 && can_share_j(v.nn) && wpb >= 2 && 2 * block_lds(v, nr, ns, mech_bytes, wpb, true) <= lds_per_cu;
+}
 
 template <int NN, int G, bool P>
 static void* integrate_fn(int scheme, bool gen) {

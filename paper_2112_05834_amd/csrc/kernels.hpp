@@ -49,7 +49,8 @@ struct IntegrateArgs {
   int* n_jac;                   // evaluations of J per cell, or NULL
   int* n_fev;                   // evaluations of f per cell, or NULL
   int accumulate;               // add counters / keep first failure status
-  int cell_doubles;             // per-cell LDS area (doubles)
+  int cell_doubles;             // per-cell LDS area beside J (doubles)
+  int share_j;                  // pairs of waves take turns with one Jacobian buffer
   int wpb;                      // waves per block
   const int* perm;              // queue order (persistent) or NULL
   unsigned long long* head;     // queue head (persistent)
@@ -107,8 +108,13 @@ int integrate_wide_blocks_per_cu(bool persistent, size_t lds_bytes);
 
 // Which compiled variants exist for a state size n (returns count, fills out).
 int variants_for(int n, Variant* out, int max_out);
-// Per-cell LDS doubles for a variant and mechanism.
+// Per-cell LDS doubles beside the Jacobian, for a variant and mechanism.
 int cell_doubles(int nn, int nr, int ns);
+// LDS bytes of a block of wpb waves, each cell with a Jacobian buffer of its
+// own, or (share_j) each pair of waves.
+size_t block_lds(const Variant& v, int nr, int ns, int mech_bytes, int wpb, bool share_j);
+// Whether the integration kernel shares Jacobian buffers at this block size.
+bool share_j(const Variant& v, int nr, int ns, int mech_bytes, int wpb, size_t lds_per_cu);
 
 hipError_t launch_integrate(const Variant& v, bool persistent, int grid, const IntegrateArgs& a,
                             size_t lds_bytes, hipStream_t st);
