@@ -108,6 +108,7 @@ struct chem_solver {
   int ns = 0, nr = 0, n = 0;
   chemk::MechArgs margs{};
   void* d_blob = nullptr;
+  void* d_rec = nullptr;
   double* d_nasa = nullptr;
   double* d_W = nullptr;
   unsigned long long* d_head = nullptr;   // [0] queue head, [1] log head
@@ -284,6 +285,10 @@ int chem_solver_create(const chem_mech* m, const chem_opts* o, int32_t dev, chem
   s->mech_fp = fnv1a(P.W.data(), P.W.size() * sizeof(double), s->mech_fp);
   HIP_TRY(hipMalloc(&s->d_blob, P.blob.size()), "hipMalloc");
   HIP_TRY(hipMemcpy(s->d_blob, P.blob.data(), P.blob.size(), hipMemcpyHostToDevice), "hipMemcpy");
+  if (!P.rec.empty()) {
+    HIP_TRY(hipMalloc(&s->d_rec, P.rec.size()), "hipMalloc");
+    HIP_TRY(hipMemcpy(s->d_rec, P.rec.data(), P.rec.size(), hipMemcpyHostToDevice), "hipMemcpy");
+  }
   HIP_TRY(hipMalloc(&s->d_nasa, P.nasa.size() * sizeof(double)), "hipMalloc");
   HIP_TRY(hipMemcpy(s->d_nasa, P.nasa.data(), P.nasa.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
   HIP_TRY(hipMalloc(&s->d_W, P.W.size() * sizeof(double)), "hipMalloc");
@@ -306,6 +311,8 @@ int chem_solver_create(const chem_mech* m, const chem_opts* o, int32_t dev, chem
   a.blob_bytes = static_cast<int>(P.blob.size());
   a.lds_bytes = P.lds_bytes;
   a.blob = static_cast<const uint4*>(s->d_blob);
+  a.rec = static_cast<const double2*>(s->d_rec);
+  a.rec_n = P.rec_n;
   a.nasa = s->d_nasa;
   a.W = s->d_W;
   if (int rc = chem_model::init(s->model)) return fail(rc, chem_model::last_error());
@@ -344,6 +351,7 @@ void chem_solver_free(chem_solver* s) {
   clear_timing(s);
   chem_model::release(s->model);
   hipFree(s->d_blob);
+  hipFree(s->d_rec);
   hipFree(s->d_nasa);
   hipFree(s->d_W);
   hipFree(s->d_head);

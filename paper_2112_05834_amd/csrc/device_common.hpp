@@ -289,6 +289,60 @@ __device__ __forceinline__ RateCore rate_core(const MechLds& L, const uint4 w, c
   return RateCore{kf, kr, Pf, Pr, q0, dlnkf, sumh};
 }
 
+// Third-body (type 1) or Troe falloff (type 2) factor theta of a rate, with
+// JAC also beta = dtheta/d[M] (times k0/kinf for falloff) and dtheta/dT. ww is
+// the reaction's efficiency and Troe word.
+template <bool JAC>
+__device__ __forceinline__ void theta_of(const MechLds& L, const double* C, int type, unsigned ww, double kf,
+                                         double dlnkf, double T, double rT, double lnT, double Ctot, double& theta,
+                                         double& beta, double& dthdT) {
+  double M = Ctot;
+  const int eoff = ww & 0xffff, neff = (ww >> 16) & 0xff;
+  M = third_body(L, C, M, eoff, neff);
+  if (type == 1) {
+    theta = M;
+    beta = 1.0;
+  } else {
+    const double* tr = L.troe + 8 * ((ww >> 24) & 0xff);
+    const double k0 = exp(tr[0] + tr[1] * lnT - tr[2] * rT);
+    const double dlnk0 = (tr[1] + tr[2] * rT) * rT;
+    double Prd = k0 * M / kf;
+    if (Prd < 1e-300) Prd = 1e-300;
+    const double ta = tr[3];
+    const double e3 = exp(-T * tr[4]), e1 = exp(-T * tr[5]);
+    double Fc = (1.0 - ta) * e3 + ta * e1;
+    double dFc = -(1.0 - ta) * tr[4] * e3 - ta * tr[5] * e1;
+    if (tr[7] != 0.0) {
+      const double e2 = exp(-tr[6] * rT);
+      Fc = Fc + e2;
+      dFc = dFc + tr[6] * rT * rT * e2;
+    }
+    if (Fc < 1e-300) Fc = 1e-300;
+    const double Lc = log10(Fc);
+    const double c = -0.4 - 0.67 * Lc;
+    const double N = 0.75 - 1.27 * Lc;
+    const double X = log10(Prd) + c;
+    const double den = N - 0.14 * X;
+    const double f1 = X / den;
+    const double opf = 1.0 + f1 * f1;
+    const double lgF = Lc / opf;
+    const double F = exp(lgF * kLn10);
+    const double lind = Prd / (1.0 + Prd);
+    theta = lind * F;
+    if (JAC) {
+      const double dlogF_dX = -Lc * 2.0 * f1 / (opf * opf) * (N / (den * den));
+      const double dlogF_dPr = dlogF_dX / (Prd * kLn10);
+      const double dPhi = F / ((1.0 + Prd) * (1.0 + Prd)) + lind * F * kLn10 * dlogF_dPr;
+      beta = dPhi * k0 / kf;
+      const double dPr_dT = Prd * (dlnk0 - dlnkf);
+      const double dL_dT = dFc / (Fc * kLn10);
+      const double df1_dL = (-0.67 * den - X * (-1.27 + 0.14 * 0.67)) / (den * den);
+      const double dlogF_dL = 1.0 / opf - Lc * 2.0 * f1 * df1_dL / (opf * opf);
+      dthdT = dPhi * dPr_dT + lind * (F * kLn10 * dlogF_dL * dL_dT);
+    }
+  }
+}
+
 template <bool JAC, bool STORE = true>
 __device__ __forceinline__ RateOut rate_finish(const MechLds& L, const uint4 w, const RateCore& rc, const double* C,
                                                double* RB, int nr, int rx, double T, double rT, double lnT,
@@ -298,53 +352,7 @@ __device__ __forceinline__ RateOut rate_finish(const MechLds& L, const uint4 w, 
   const int dnu = static_cast<int>((w.z >> 24) & 0x7f) - 64;
   const double kf = rc.kf, kr = rc.kr, Pf = rc.Pf, Pr = rc.Pr, q0 = rc.q0, dlnkf = rc.dlnkf, sumh = rc.sumh;
   double theta = 1.0, beta = 0.0, dthdT = 0.0;
-  if (type >= 1) {
-    double M = Ctot;
-    const int eoff = w.w & 0xffff, neff = (w.w >> 16) & 0xff;
-    M = third_body(L, C, M, eoff, neff);
-    if (type == 1) {
-      theta = M;
-      beta = 1.0;
-    } else {
-      const double* tr = L.troe + 8 * ((w.w >> 24) & 0xff);
-      const double k0 = exp(tr[0] + tr[1] * lnT - tr[2] * rT);
-      const double dlnk0 = (tr[1] + tr[2] * rT) * rT;
-      double Prd = k0 * M / kf;
-      if (Prd < 1e-300) Prd = 1e-300;
-      const double ta = tr[3];
-      const double e3 = exp(-T * tr[4]), e1 = exp(-T * tr[5]);
-      double Fc = (1.0 - ta) * e3 + ta * e1;
-      double dFc = -(1.0 - ta) * tr[4] * e3 - ta * tr[5] * e1;
-      if (tr[7] != 0.0) {
-        const double e2 = exp(-tr[6] * rT);
-        Fc = Fc + e2;
-        dFc = dFc + tr[6] * rT * rT * e2;
-      }
-      if (Fc < 1e-300) Fc = 1e-300;
-      const double Lc = log10(Fc);
-      const double c = -0.4 - 0.67 * Lc;
-      const double N = 0.75 - 1.27 * Lc;
-      const double X = log10(Prd) + c;
-      const double den = N - 0.14 * X;
-      const double f1 = X / den;
-      const double opf = 1.0 + f1 * f1;
-      const double lgF = Lc / opf;
-      const double F = exp(lgF * kLn10);
-      const double lind = Prd / (1.0 + Prd);
-      theta = lind * F;
-      if (JAC) {
-        const double dlogF_dX = -Lc * 2.0 * f1 / (opf * opf) * (N / (den * den));
-        const double dlogF_dPr = dlogF_dX / (Prd * kLn10);
-        const double dPhi = F / ((1.0 + Prd) * (1.0 + Prd)) + lind * F * kLn10 * dlogF_dPr;
-        beta = dPhi * k0 / kf;
-        const double dPr_dT = Prd * (dlnk0 - dlnkf);
-        const double dL_dT = dFc / (Fc * kLn10);
-        const double df1_dL = (-0.67 * den - X * (-1.27 + 0.14 * 0.67)) / (den * den);
-        const double dlogF_dL = 1.0 / opf - Lc * 2.0 * f1 * df1_dL / (opf * opf);
-        dthdT = dPhi * dPr_dT + lind * (F * kLn10 * dlogF_dL * dL_dT);
-      }
-    }
-  }
+  if (type >= 1) theta_of<JAC>(L, C, type, w.w, kf, dlnkf, T, rT, lnT, Ctot, theta, beta, dthdT);
   RateOut o{theta * q0, 0.0, 0.0, 0.0, 0.0};
   if (JAC) {
     const double dlnkr = rev ? dlnkf - (sumh * rT - dnu * rT) : 0.0;

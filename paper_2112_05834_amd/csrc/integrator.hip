@@ -184,14 +184,15 @@ struct Grp {
 
 // A block's LDS after the mechanism image: one Jacobian J [NN*NN] row-major
 // per cell, or per pair of waves that take turns with it (below), then every
-// cell's own area: the pivot-row buffer P [NN+1 rounded to even], a
-// reaction/species buffer RB, then the per-species vectors C, gRT, hRT [NN-1
-// each; entries from ns on are zero, so column loops run to NN-1 without a
-// bound check]. RB holds, for state sizes up to 32, the per-reaction rate of
-// progress (and with the Jacobian kf*theta, kr*theta, q0*dtheta/d[M], dq/dT)
-// read by the species pass [max(5*nr, 3*NN)]; above 32 only the species sums
-// omega, d omega/dT and sum nu q0 dtheta/d[M] [3*NN] that the reaction lanes
-// add into.
+// cell's own area: the per-species vectors C, gRT, hRT [NN each; entry ns is
+// the absent species of the reaction records (C = 1, g = h = 0), entries
+// after it are zero, so column loops run without a bound check] and a
+// reaction/species buffer RB. RB holds, for state sizes up to 32, the
+// per-reaction rate of progress (and with the Jacobian kf*theta, kr*theta,
+// q0*dtheta/d[M], dq/dT) read by the species pass [max(5*nr, 3*NN)]; above 32
+// only the species sums omega, d omega/dT and sum nu q0 dtheta/d[M] [3*NN]
+// that the reaction lanes add into.
+// P is a buffer of the species pass's own (up to 32), and the LU's.
 struct CellArea {
   double* J;
   double* P;
@@ -203,8 +204,9 @@ struct CellArea {
 
 __host__ __device__ constexpr int pbuf_doubles(int nn) { return (nn + 2) & ~1; }
 // The LU's pivot rows of one panel, interleaved (column j's four entries side
-// by side, up to a multiple of 16 columns), sit in P and run on into RB and
-// the species vectors, which hold nothing between two right-hand sides.
+// by side, up to a multiple of 16 columns), sit at the start of the cell's own
+// area above 32 state components (it holds nothing between two right-hand
+// sides), otherwise in P.
 constexpr int kPanel = 4;
 __host__ __device__ constexpr int lu_rows_doubles(int nn) { return kPanel * ((nn + 15) & ~15); }
 // state sizes above 32 assemble rates and Jacobian reaction by reaction
@@ -212,9 +214,11 @@ __host__ __device__ constexpr bool reaction_major(int nn) { return nn > 32; }
 __host__ __device__ constexpr int rbuf_doubles(int nn, int nr) {
   return reaction_major(nn) ? 3 * nn : (5 * nr > 3 * nn ? 5 * nr : 3 * nn);
 }
-__host__ __device__ constexpr int cell_doubles_c(int nn, int nr, int ns) {
-  const int rest = pbuf_doubles(nn) + rbuf_doubles(nn, nr) + 3 * (nn - 1);
-  return ((rest > lu_rows_doubles(nn) ? rest : lu_rows_doubles(nn)) + 1) & ~1;
+__host__ __device__ constexpr int cell_doubles_c(int nn, int nr) {
+  const int vec = 3 * nn + rbuf_doubles(nn, nr);
+  const int pb = lu_rows_doubles(nn) > pbuf_doubles(nn) ? lu_rows_doubles(nn) : pbuf_doubles(nn);
+  const int all = reaction_major(nn) ? (vec > pb ? vec : pb) : ((vec + 1) & ~1) + pb;
+  return (all + 1) & ~1;
 }
 __host__ __device__ constexpr int j_doubles_c(int nn) { return (nn * nn + 1) & ~1; }
 // Sizes whose waves may share a Jacobian buffer in pairs: one cell per wave,
@@ -225,11 +229,11 @@ template <int NN>
 __device__ __forceinline__ CellArea cell_area(double* J, double* base, int nr) {
   CellArea c;
   c.J = J;
-  c.P = base;
-  c.RB = c.P + pbuf_doubles(NN);
-  c.C = c.RB + rbuf_doubles(NN, nr);
-  c.gRT = c.C + (NN - 1);
-  c.hRT = c.gRT + (NN - 1);
+  c.C = base;
+  c.gRT = base + NN;
+  c.hRT = base + 2 * NN;
+  c.RB = base + 3 * NN;
+  c.P = reaction_major(NN) ? base : base + ((3 * NN + rbuf_doubles(NN, nr) + 1) & ~1);
   return c;
 }
 
@@ -354,18 +358,187 @@ struct Cell {
   // whose order of additions does not depend on the group width.
   static constexpr bool kScatter = reaction_major(NN);
 
-  // f = dy/dt at y (this lane's component); with JAC also the analytical
-  // Jacobian df/dy, written row-major into ca.J (complete on return).
+  // Reactions of the reaction-major assembly from the packed records: block
+  // by block of 64, one lane per reaction, in the order of the general records
+  // (rx_scatter below them), with the same operations per reaction. The
+  // records hold what the general words make every lane decode: LDS offsets
+  // of the species slots (one register serves C, g, h and the sums, by
+  // instruction offsets), factors of the mass-action products without selects
+  // on the orders, orders as doubles. Products by orders 1 and 2 are exact, so
+  // they may be fused. Third slots and factors are handled only in blocks that
+  // have any.
   template <bool JAC>
-  __device__ static __forceinline__ double rhs(const MechArgs& A, const MechLds& L, const CellArea& ca,
-                                               double p, double y) {
+  __device__ static __forceinline__ void reactions(const MechArgs& A, const MechLds& L, const CellArea& ca, double T,
+                                                   double rT, double lnT, double lnRTp, double Ctot) {
+    const int i = Gp::lane();
+    const double2* rec = A.rec + i;
+    const int N = A.rec_n;
+    char* const Cb = reinterpret_cast<char*>(ca.C);
+    char* const Jb = reinterpret_cast<char*>(ca.J + NN + 1);
+    constexpr int kG = 8 * NN, kH = 16 * NN, kOm = 24 * NN, kWT = 32 * NN, kTd = 40 * NN;   // byte offsets from C
+    const auto at = [&](unsigned off, int arr) { return *reinterpret_cast<const double*>(Cb + off + arr); };
+#pragma nounroll
+    for (int r0 = 0; r0 < N; r0 += 64, rec += 64) {
+      const double2 k1 = rec[0], k2 = rec[N], n0 = rec[2 * N], n1 = rec[3 * N];
+      const uint4 w0 = reinterpret_cast<const uint4*>(rec)[5 * N];
+      const int type = (w0.w >> 8) & 3;
+      const bool rev = (w0.w >> 10) & 1;
+      const bool third = __any(w0.w & (4u | 32u | 64u));    // uniform: a third slot or factor in this block
+      double2 n2{0.0, 0.0};
+      uint4 w1{0, 0, 0, 0};
+      if (__any(type != 0) || third) w1 = reinterpret_cast<const uint4*>(rec)[6 * N];
+      const unsigned f0 = w0.x & 0xffff, f1 = w0.x >> 16, p0 = w0.y & 0xffff, p1 = w0.y >> 16;
+      const double cf0 = at(f0, 0), cp0 = at(p0, 0);
+      double cf1 = at(w0.z & 0xffff, 0), cp1 = at(w0.z >> 16, 0);
+      const double lnkf = k1.x + k1.y * lnT - k2.x * rT;
+      const double kf = exp(lnkf);
+      double sumg = fma(-n0.x, at(f0, kG), 0.0);
+      sumg = fma(n0.y, at(p0, kG), sumg);
+      sumg = fma(-n1.x, at(f1, kG), sumg);
+      sumg = fma(n1.y, at(p1, kG), sumg);
+      double sumh = 0.0;
+      if (JAC) {
+        sumh = fma(-n0.x, at(f0, kH), 0.0);
+        sumh = fma(n0.y, at(p0, kH), sumh);
+        sumh = fma(-n1.x, at(f1, kH), sumh);
+        sumh = fma(n1.y, at(p1, kH), sumh);
+      }
+      double Pf = cf0 * cf1, Pr = cp0 * cp1;
+      double cf2 = 1.0, cp2 = 1.0;
+      if (third) {
+        const unsigned f2 = w1.x & 0xffff, p2 = w1.x >> 16;
+        n2 = rec[4 * N];
+        cf2 = at(w1.y & 0xffff, 0);
+        cp2 = at(w1.y >> 16, 0);
+        Pf = Pf * cf2;
+        Pr = Pr * cp2;
+        sumg = fma(-n2.x, at(f2, kG), sumg);
+        sumg = fma(n2.y, at(p2, kG), sumg);
+        if (JAC) {
+          sumh = fma(-n2.x, at(f2, kH), sumh);
+          sumh = fma(n2.y, at(p2, kH), sumh);
+        }
+      }
+      // kr = kf / Kc with Kc = exp(-sum nu g/RT) (p_atm/RT)^(sum nu)
+      double kr = exp(fma(k2.y, lnRTp, lnkf + sumg));
+      kr = rev ? kr : 0.0;
+      const double q0 = kf * Pf - kr * Pr;
+      const double dlnkf = (k1.y + k2.x * rT) * rT;
+      double theta = 1.0, beta = 0.0, dthdT = 0.0;
+      if (type >= 1) theta_of<JAC>(L, ca.C, type, w1.z, kf, dlnkf, T, rT, lnT, Ctot, theta, beta, dthdT);
+      const double q = theta * q0;
+      double kfT = 0.0, krT = 0.0, q0b = 0.0, dqdT = 0.0;
+      if (JAC) {
+        const double dlnkr = rev ? dlnkf - (sumh * rT - k2.y * rT) : 0.0;
+        kfT = kf * theta;
+        krT = kr * theta;
+        q0b = q0 * beta;
+        dqdT = theta * (kf * dlnkf * Pf - kr * dlnkr * Pr) + q0 * dthdT;
+      }
+      // slots f0 f1 f2 p0 p1 p2: species sums, then J by row and column
+      const double nu[6] = {-n0.x, -n1.x, -n2.x, n0.y, n1.y, n2.y};
+      const unsigned off[6] = {f0, f1, w1.x & 0xffff, p0, p1, w1.x >> 16};
+      const auto each = [&](auto&& fn) {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+          if (a % 3 == 2 && !third) continue;
+          if (w0.w & (1u << a)) fn(a);
+        }
+      };
+      each([&](int a) {
+        double* om = reinterpret_cast<double*>(Cb + off[a] + kOm);
+        lds_add(om, nu[a] * q);
+        if (JAC) {
+          lds_add(om + NN, nu[a] * dqdT);
+          if (type >= 1) lds_add(om + 2 * NN, nu[a] * q0b);
+        }
+      });
+      if (JAC) {
+        double dq[6];
+        dq[0] = kfT * (n0.x * cf1);
+        dq[1] = kfT * cf0;
+        dq[3] = -(krT * (n0.y * cp1));
+        dq[4] = -(krT * cp0);
+        dq[2] = dq[5] = 0.0;
+        if (third) {
+          dq[0] = kfT * (n0.x * cf1 * cf2);
+          dq[1] = kfT * (cf0 * cf2);
+          dq[2] = kfT * (cf0 * cf1);
+          dq[3] = -(krT * (n0.y * cp1 * cp2));
+          dq[4] = -(krT * (cp0 * cp2));
+          dq[5] = -(krT * (cp0 * cp1));
+        }
+        each([&](int a) {
+          char* Jr = Jb + off[a] * NN;
+#pragma unroll
+          for (int b = 0; b < 6; ++b) {
+            if (b % 3 == 2 && !third) continue;
+            if (w0.w & (1u << b)) lds_add(reinterpret_cast<double*>(Jr + off[b]), nu[a] * dq[b]);
+          }
+        });
+        if (type >= 1) {
+          const int eoff = w1.z & 0xffff, neff = (w1.z >> 16) & 0xff;
+          for (int e0 = 0; e0 < neff; e0 += kEffChunk) {
+            int sp[kEffChunk];
+            double am[kEffChunk];
+#pragma unroll
+            for (int c = 0; c < kEffChunk; ++c) {
+              const int e = e0 + c < neff ? eoff + e0 + c : eoff;
+              sp[c] = 8 * L.eff_sp[e];
+              am[c] = L.eff_am1[e];
+            }
+            each([&](int a) {
+              char* Jr = Jb + off[a] * NN;
+              const double ab = nu[a] * q0b;
+#pragma unroll
+              for (int c = 0; c < kEffChunk; ++c)
+                if (e0 + c < neff) lds_add(reinterpret_cast<double*>(Jr + sp[c]), ab * am[c]);
+            });
+          }
+        }
+      }
+    }
+  }
+
+  // The same from the general records (any orders).
+  template <bool JAC>
+  __device__ static __forceinline__ void reactions_general(const MechArgs& A, const MechLds& L, const CellArea& ca,
+                                                           double T, double rT, double lnT, double lnRTp,
+                                                           double Ctot) {
+    const int nr = A.nr, i = Gp::gl();
+    double* const om = ca.RB;
+#pragma nounroll
+    for (int rx = i; rx < nr; rx += G) {
+      const uint4 w = L.rint[rx];
+      const RateOut r = reaction_rate<JAC, false>(L, w, ca.C, ca.gRT, ca.hRT, ca.RB, nr, rx, T, rT, lnT, lnRTp, Ctot);
+      rx_scatter<NN, JAC>(L, ca.C, w, r, om, om + NN, om + 2 * NN, ca.J);
+    }
+  }
+
+  // f = dy/dt at y (this lane's component); with JAC also the analytical
+  // Jacobian df/dy: written row-major into ca.J (complete on return), or with
+  // TOM straight into M = g I - J, this lane's row in registers. jlock guards
+  // a shared ca.J; with TOM it is held from the first write of ca.J until M is
+  // formed.
+  template <bool JAC>
+  __device__ static __forceinline__ double rhs(const MechArgs& A, const MechLds& L, const CellArea& ca, double p,
+                                               double y) {
+    double none[NN];
+    return eval<JAC, false>(A, L, ca, p, y, nullptr, 0.0, none);
+  }
+
+  template <bool JAC, bool TOM>
+  __device__ static __forceinline__ double eval(const MechArgs& A, const MechLds& L, const CellArea& ca, double p,
+                                                double y, int* jlock, double g, double (&M)[NN]) {
     const int ns = A.ns, nr = A.nr;
     const int i = Gp::gl();                 // state component of this lane
     const bool sp = i >= 1 && i <= ns;      // lane holds species i-1
     const int s = sp ? i - 1 : 0;
     const double T = Gp::bcast(y, 0);
     const double rT = 1.0 / T;
-    const double lnT = log(T);
+    // ln T and ln(RT/p_atm) by one logarithm, on lanes 0 and 1
+    const double lns = log(i == 1 ? kR * T / kPatm : T);
+    const double lnT = Gp::bcast(lns, 0), lnRTp = Gp::bcast(lns, 1);
     // mixture state
     const double Ys = sp ? y : 0.0;
     const double rWs = sp ? L.rW[s] : 0.0;
@@ -373,30 +546,24 @@ struct Cell {
     const double Wbar = 1.0 / invWbar;
     const double rho = p * Wbar / (kR * T);
     const double Cs = rho * Ys * rWs;
-    const bool pad = i > ns && i < NN;      // padding component of a padded state size
-    if (sp) ca.C[s] = Cs;
     const double Ctot = Gp::sum(Cs);
     // species thermo (NASA-7, range by T < Tmid)
     double cpR = 0.0, hRT = 0.0, dcpR = 0.0;
     if (sp) {
       double gRT;
       nasa7<JAC>(A.nasa + 16 * s, T, rT, lnT, cpR, hRT, gRT, dcpR);
+      ca.C[s] = Cs;
       ca.gRT[s] = gRT;
       ca.hRT[s] = hRT;
-    } else if (pad) {
-      ca.C[i - 1] = 0.0;
-      ca.gRT[i - 1] = 0.0;
-      ca.hRT[i - 1] = 0.0;
+    } else if (i < NN) {
+      // the absent species, and the padding components of a padded state size
+      const int k = i == 0 ? NN - 1 : i - 1;
+      ca.C[k] = k == ns ? 1.0 : 0.0;
+      ca.gRT[k] = 0.0;
+      ca.hRT[k] = 0.0;
     }
     const double cp = Gp::sum(Ys * cpR * kR * rWs);
     double dcp = 0.0;
-    if (JAC) {
-      dcp = Gp::sum(Ys * dcpR * kR * rWs);
-      if (i < NN) {
-#pragma unroll
-        for (int j = 0; j < NN; ++j) ca.J[i * NN + j] = 0.0;
-      }
-    }
     // species sums of the reaction-major assembly
     double* const som = ca.RB;
     double* const swT = ca.RB + NN;
@@ -408,34 +575,27 @@ struct Cell {
         std_[i] = 0.0;
       }
     }
+    if (JAC) {
+      dcp = Gp::sum(Ys * dcpR * kR * rWs);
+      if (TOM) j_acquire(jlock);
+      if constexpr (kScatter) {
+        double2* z = reinterpret_cast<double2*>(ca.J);
+#pragma unroll
+        for (int e = 0; e < j_doubles_c(NN) / 2; e += 64)
+          if (e + 64 <= j_doubles_c(NN) / 2 || e + i < j_doubles_c(NN) / 2) z[e + i] = double2{0.0, 0.0};
+      } else if (i < NN) {
+#pragma unroll
+        for (int j = 0; j < NN; ++j) ca.J[i * NN + j] = 0.0;
+      }
+    }
     wsync();
 
     // ---- reactions: one lane per reaction ----
-    const double lnRTp = log(kR * T / kPatm);
     if constexpr (kScatter) {
-      // two blocks of reactions per pass, their rate evaluations interleaved
-      // (independent work for the one wave on the SIMD); the adds follow in
-      // block order
-      int r0 = 0;
-      for (; r0 + G < nr; r0 += 2 * G) {
-        const int rxa = r0 + i;
-        const int rxb = rxa + G;
-        const bool vb = rxb < nr;
-        const int rxb_c = vb ? rxb : rxa;
-        const uint4 wa = L.rint[rxa];
-        const uint4 wb = L.rint[rxb_c];
-        const RateCore ka = rate_core<JAC>(L, wa, ca.C, ca.gRT, ca.hRT, rxa, rT, lnT, lnRTp);
-        const RateCore kb = rate_core<JAC>(L, wb, ca.C, ca.gRT, ca.hRT, rxb_c, rT, lnT, lnRTp);
-        const RateOut ra = rate_finish<JAC, false>(L, wa, ka, ca.C, ca.RB, nr, rxa, T, rT, lnT, Ctot);
-        const RateOut rb = rate_finish<JAC, false>(L, wb, kb, ca.C, ca.RB, nr, rxb_c, T, rT, lnT, Ctot);
-        rx_scatter<NN, JAC>(L, ca.C, wa, ra, som, swT, std_, ca.J);
-        if (vb) rx_scatter<NN, JAC>(L, ca.C, wb, rb, som, swT, std_, ca.J);
-      }
-      if (r0 < nr && r0 + i < nr) {
-        const int rx = r0 + i;
-        const uint4 w = L.rint[rx];
-        const RateOut r = reaction_rate<JAC, false>(L, w, ca.C, ca.gRT, ca.hRT, ca.RB, nr, rx, T, rT, lnT, lnRTp, Ctot);
-        rx_scatter<NN, JAC>(L, ca.C, w, r, som, swT, std_, ca.J);
+      if (A.rec) {
+        reactions<JAC>(A, L, ca, T, rT, lnT, lnRTp, Ctot);
+      } else {
+        reactions_general<JAC>(A, L, ca, T, rT, lnT, lnRTp, Ctot);
       }
     } else {
       for (int r0 = 0; r0 < nr; r0 += G) {
@@ -521,7 +681,7 @@ struct Cell {
     if (sp) {
       const double* Jrow = ca.J + i * NN + 1;
       double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-      // columns from ns on are zero in J and in C
+      // columns from ns on are zero in J
 #pragma unroll
       for (int k = 0; k < NN - 1; k += 4) {
         a0 = fma(Jrow[k], ca.C[k], a0);
@@ -552,26 +712,67 @@ struct Cell {
       JT = -(dQdY + fT * drcp) / rcp;
     }
     wsync();
-    if (sp) {
-      double* Jrow = ca.J + i * NN;
-      const double Wi_rho = A.W[s] / rho;
-      // rW is zero from ns on (up to 64 entries), which keeps the padding
-      // columns of J zero
+    const double Wi_rho = sp ? A.W[s] / rho : 0.0;
+    const double JcT = sp ? Wi_rho * (wT - sv / T) + fY / T
+                          : (i == 0 ? -(dQdT + fT * (-rcp / T + rho * dcp)) / rcp : 0.0);   // column 0
+    // rW is zero from ns on (up to 64 entries), which keeps the padding
+    // columns of J zero
+    if constexpr (TOM) {
+      // The column factors rho/W_k, Wbar/W_k and 1/W_k, formed once by lane
+      // k, are read back as broadcasts; -J goes straight into the rows of M,
+      // g is added on the diagonal (one lane per instruction), and lane 0
+      // reads its row, the T row, from where the other lanes left it.
+      double* const fac = ca.C;     // C, g and h are not needed any more
+      const double rWi = i < NN - 1 ? L.rW[i] : 0.0;
+      if (i < NN - 1) *reinterpret_cast<double2*>(fac + 2 * i) = double2{rho * rWi, Wbar * rWi};
+      if (sp) ca.J[i] = -JT;
+      wsync();
+      const double fYW = fY * Wbar;
+      M[0] = -JcT;
+      if (i < NN) {
+        const double* Jrow = ca.J + i * NN;
 #pragma unroll
-      for (int k = 0; k < NN - 1; ++k) {
-        const double rWk = L.rW[k];
-        const double D = Jrow[1 + k] + td;
-        const double dw = (rho * rWk) * D - (Wbar * rWk) * sv;
-        Jrow[1 + k] = Wi_rho * dw + fY * Wbar * rWk;
+        for (int k = 0; k < NN - 1; ++k) {
+          const double2 ab = *reinterpret_cast<const double2*>(fac + 2 * k);
+          const double D = Jrow[1 + k] + td;
+          const double dw = ab.x * D - ab.y * sv;
+          M[1 + k] = -(Wi_rho * dw + fYW * L.rW[k]);
+        }
+        if (i == 0) {
+#pragma unroll
+          for (int k = 1; k < NN; ++k) M[k] = ca.J[k];
+        }
+      } else {
+#pragma unroll
+        for (int k = 1; k < NN; ++k) M[k] = 0.0;
       }
-      Jrow[0] = Wi_rho * (wT - sv / T) + fY / T;
-      ca.J[i] = JT;
-    } else if (i == 0) {
-      const double drcp = -rcp / T + rho * dcp;
-      ca.J[0] = -(dQdT + fT * drcp) / rcp;
+      j_release(jlock);
+      static_for<NN>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        add_on_lane<j>(M[j], g);
+      });
+    } else {
+      if (sp) {
+        double* Jrow = ca.J + i * NN;
+#pragma unroll
+        for (int k = 0; k < NN - 1; ++k) {
+          const double rWk = L.rW[k];
+          const double D = Jrow[1 + k] + td;
+          const double dw = (rho * rWk) * D - (Wbar * rWk) * sv;
+          Jrow[1 + k] = Wi_rho * dw + fY * Wbar * rWk;
+        }
+        ca.J[i] = JT;
+      }
+      if (sp || i == 0) ca.J[i * NN] = JcT;
+      wsync();
     }
-    wsync();
     return f;
+  }
+
+  // v += g on lane J alone (all 64 lanes active before and after)
+  template <int J>
+  __device__ static __forceinline__ void add_on_lane(double& v, double g) {
+    asm volatile("s_bfm_b64 exec, 1, %2\n\tv_add_f64 %0, %0, %1\n\ts_mov_b64 exec, -1" : "+v"(v) : "v"(g), "n"(J));
   }
 
   // Without the bath gas (the last species, lane ns) its mass fraction is
@@ -949,29 +1150,35 @@ struct Cell {
         status = 2;
         break;
       }
-      // f and J of the step start. A buffer of the wave's own keeps J across
-      // rejected attempts; a shared one may have been overwritten, and the
-      // same J is formed again (a few per cent of the attempts).
-      j_acquire(jlock);
-      if (need || jlock) {
-        if (GEN && o.jac_fd) {
-          f0 = rhs<false>(A, L, ca, p, y);
-          fd_jacobian(A, L, ca, p, y, f0, nb);
-        } else {
-          f0 = rhs<true>(A, L, ca, p, y);
-          if (nb) reduce_bath(ca, ns);
-        }
-        need = false;
-      }
       const double g = 1.0 / (TB::gamma * hc);
-      if (i < NN) {
-#pragma unroll
-        for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - ca.J[i * NN + j];
+      if constexpr (kScatter && !GEN) {
+        // f of the step start and M = g I - J, formed together; after a
+        // rejected attempt (a few per cent) J is formed again
+        f0 = eval<true, true>(A, L, ca, p, y, jlock, g, M);
+        need = false;
       } else {
+        // f and J of the step start. A buffer of the wave's own keeps J
+        // across rejected attempts; a shared one may have been overwritten
+        j_acquire(jlock);
+        if (need || jlock) {
+          if (GEN && o.jac_fd) {
+            f0 = rhs<false>(A, L, ca, p, y);
+            fd_jacobian(A, L, ca, p, y, f0, nb);
+          } else {
+            f0 = rhs<true>(A, L, ca, p, y);
+            if (nb) reduce_bath(ca, ns);
+          }
+          need = false;
+        }
+        if (i < NN) {
 #pragma unroll
-        for (int j = 0; j < NN; ++j) M[j] = 0.0;
+          for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - ca.J[i * NN + j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < NN; ++j) M[j] = 0.0;
+        }
+        j_release(jlock);
       }
-      j_release(jlock);
       const int info = lu(M, pos, rdiag, ca.P, nullptr);
       ++att;
       if (info) {
@@ -1274,12 +1481,12 @@ int variants_for(int n, Variant* out, int max_out) {
   return cnt;
 }
 
-int cell_doubles(int nn, int nr, int ns) { return cell_doubles_c(nn, nr, ns); }
+int cell_doubles(int nn, int nr, int ns) { return cell_doubles_c(nn, nr); }
 
 size_t block_lds(const Variant& v, int nr, int ns, int mech_bytes, int wpb, bool share_j) {
   const int cpw = 64 / v.g;
   const size_t nj = share_j ? (wpb + 1) / 2 : wpb * cpw;
-  return mech_bytes + sizeof(double) * (nj * j_doubles_c(v.nn) + static_cast<size_t>(wpb) * cpw * cell_doubles_c(v.nn, nr, ns)) +
+  return mech_bytes + sizeof(double) * (nj * j_doubles_c(v.nn) + static_cast<size_t>(wpb) * cpw * cell_doubles_c(v.nn, nr)) +
          (share_j ? 16 : 0);
 }
 

@@ -15,6 +15,8 @@ struct MechArgs {
   int blob_bytes;          // multiple of 16
   int lds_bytes;           // leading part of the blob staged in LDS (multiple of 16)
   const uint4* blob;       // global copy of the image
+  const double2* rec;      // reaction records of the per-wave kernel, NULL: general records only
+  int rec_n;               // entries per record array
   const double* nasa;      // [ns][16]
   const double* W;         // [ns]
 };

@@ -314,6 +314,62 @@ Packed pack(const MechHost& m) {
   std::vector<double> rW(ns);
   for (int s = 0; s < ns; ++s) rW[s] = 1.0 / m.W[s];
   put(P.off_rW, rW.data(), 8 * ns);
+  // records of the per-wave kernel (see mech.hpp)
+  {
+    const int n64 = (nr + 63) / 64 * 64;
+    std::vector<double> d(static_cast<size_t>(n64) * 10, 0.0);
+    std::vector<uint32_t> w(static_cast<size_t>(n64) * 8, 0);
+    const uint32_t none = 8u * static_cast<uint32_t>(ns);
+    bool fits = ns <= 63;
+    for (int r = 0; r < n64 && fits; ++r) {
+      uint32_t slot[6] = {none, none, none, none, none, none}, e2[2] = {none, none}, e3[2] = {none, none}, flags = 0;
+      if (r < nr) {
+        const Rxn& x = m.rx[order[r]];
+        d[2 * r] = lnA[r];
+        d[2 * r + 1] = bb[r];
+        d[2 * (n64 + r)] = EaR[r];
+        double dnu = 0;
+        for (int sd = 0; sd < 2; ++sd) {
+          const auto& v = sd ? x.prod : x.reac;
+          int total = 0;
+          for (size_t j = 0; j < v.size(); ++j) {
+            total += v[j].second;
+            if (v[j].second > (j == 0 ? 2 : 1)) fits = false;
+          }
+          if (total > 3) fits = false;
+          if (!fits) break;
+          // the second species of 2A + B takes slot 2, so that the factors
+          // are C[slot 0], then C[slot 0] again or C[slot 1], then C[slot 2]
+          const bool twice = v[0].second == 2;
+          for (size_t j = 0; j < v.size(); ++j) {
+            const int k = j == 0 ? 0 : (twice ? 2 : static_cast<int>(j));
+            slot[3 * sd + k] = 8u * static_cast<uint32_t>(v[j].first);
+            d[2 * ((2 + k) * n64 + r) + sd] = v[j].second;
+            flags |= 1u << (3 * sd + k);
+            dnu += (sd ? 1 : -1) * v[j].second;
+          }
+          e2[sd] = twice ? slot[3 * sd] : slot[3 * sd + 1];
+          e3[sd] = slot[3 * sd + 2];
+          if (e3[sd] != none) flags |= 64u;
+        }
+        d[2 * (n64 + r) + 1] = dnu;
+        flags |= static_cast<uint32_t>(x.type) << 8 | static_cast<uint32_t>(x.rev ? 1 : 0) << 10;
+        w[4 * (n64 + r) + 2] = rint[4 * r + 3];
+      }
+      w[4 * r] = slot[0] | slot[1] << 16;
+      w[4 * r + 1] = slot[3] | slot[4] << 16;
+      w[4 * r + 2] = e2[0] | e2[1] << 16;
+      w[4 * r + 3] = flags;
+      w[4 * (n64 + r)] = slot[2] | slot[5] << 16;
+      w[4 * (n64 + r) + 1] = e3[0] | e3[1] << 16;
+    }
+    if (fits && n64 > 0) {
+      P.rec_n = n64;
+      P.rec.resize(d.size() * sizeof(double) + w.size() * sizeof(uint32_t));
+      std::memcpy(P.rec.data(), d.data(), d.size() * sizeof(double));
+      std::memcpy(P.rec.data() + d.size() * sizeof(double), w.data(), w.size() * sizeof(uint32_t));
+    }
+  }
   P.ntroe = static_cast<int>(troe.size() / 8);
   P.neff = static_cast<int>(eff_sp.size());
   P.nent = static_cast<int>(sp_ent.size());
