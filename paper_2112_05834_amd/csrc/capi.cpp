@@ -396,17 +396,24 @@ struct Shape {
   bool share_j = false;
 };
 
-// Waves per block when the caller leaves them open. Where waves can share
-// Jacobian buffers (two blocks of four to a CU):
-// - up to 8 cells per CU, one wave each with a buffer of its own: the longest
-//   cell's chain of steps sets the time and sharing only delays it (54
-//   species, 131 cells: 18.4 against 19.5 ms, 2048 cells: 25.6 against 26.0);
-// - the static map, two: a block ends with its longest cell (16411 cells: 93
-//   ms with two, 101 with one, 123 with four).
+// Waves per block when the caller leaves them open (n cells, 0: not an
+// integration).
+// - Few waves: one each, spread over the CUs, with a Jacobian buffer of its
+//   own; the longest cell's chain of steps sets the time, and sharing a block
+//   only delays it. Up to 8 waves per CU where waves could share buffers (54
+//   species, 131 cells: 18.4 against 19.5 ms with four to a block, 2048 cells:
+//   25.6 against 26.0), up to 4 elsewhere (9 species, 1024 cells: 6.7 against
+//   7.3 ms; equal at 8192).
+// - The static map: a block ends with its longest cell, so one wave, or two
+//   where a pair shares a buffer and so doubles the waves of a CU (54 species,
+//   16411 cells: 93 ms with two, 101 with one, 123 with four).
 int auto_wpb(const chem_solver* s, const chem_opts& o, int64_t n, const chemk::Variant& v) {
-  if (n < 1 || !chemk::share_j(v, s->nr, s->ns, s->margs.lds_bytes, 4, kMaxLds)) return 4;
-  if (n <= 8LL * s->cus) return 1;
-  return o.schedule == CHEM_PLAIN ? 2 : 4;
+  if (n < 1) return 4;
+  const bool share = chemk::share_j(v, s->nr, s->ns, s->margs.lds_bytes, 4, kMaxLds);
+  const int cpw = 64 / v.g;
+  const int64_t waves = (n + cpw - 1) / cpw;
+  if (waves <= static_cast<int64_t>(share ? 8 : 4) * s->cus) return 1;
+  return o.schedule == CHEM_PLAIN ? (share ? 2 : 1) : 4;
 }
 
 // n: cells of the launch (0: not an integration)
@@ -420,9 +427,14 @@ int pick_shape(const chem_solver* s, const chem_opts& o, int64_t n, Shape& sh) {
     sh.lds = sh.lds_own = s->wide_lds;
     return CHEM_OK;
   }
-  // variant by requested cells per wave, else the first compiled one
+  // variant by requested cells per wave, else the first compiled one, or one
+  // cell per wave while that leaves no SIMD with two (9 species, 1024 cells:
+  // 5.0 against 5.2 ms; 4096 cells: 10.9 against 5.6)
   int want_g = o.cells_per_wave > 0 ? 64 / o.cells_per_wave : 0;
   sh.v = s->variants[0];
+  if (!want_g && n > 0 && n <= 4LL * s->cus)
+    for (int i = 0; i < s->nvariants; ++i)
+      if (s->variants[i].g == 64) sh.v = s->variants[i];
   if (want_g) {
     bool found = false;
     for (int i = 0; i < s->nvariants; ++i)

@@ -60,6 +60,13 @@ constexpr int kMirror = 0x140;     // lane i <-> 15-i within 16
 constexpr int kRowBcast15 = 0x142; // lane 15 of each row into the next row
 constexpr int kRowBcast31 = 0x143; // lane 31 into rows 2 and 3
 
+// v of lane SRC of each 16-lane row, to every lane of that row
+template <int SRC>
+__device__ __forceinline__ double row_bcast(double v) {
+  const long long b = __builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + SRC, 0xf, 0xf, true);
+  return __longlong_as_double(b);
+}
+
 // DPP move into the rows of ROWMASK only; the other rows keep old
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ double dpp_rows_d(double old, double v) {
@@ -70,18 +77,6 @@ __device__ __forceinline__ double dpp_rows_d(double old, double v) {
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ int dpp_rows_i(int old, int v) {
   return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWMASK, 0xf, false);
-}
-
-// largest of one 32-bit key per lane (all 64 lanes; every lane of the last
-// step reads inside the rows it takes from)
-__device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
-  x = ::max(x, static_cast<unsigned>(dpp_i<kXor1>(static_cast<int>(x))));
-  x = ::max(x, static_cast<unsigned>(dpp_i<kXor2>(static_cast<int>(x))));
-  x = ::max(x, static_cast<unsigned>(dpp_i<kHalfMirror>(static_cast<int>(x))));
-  x = ::max(x, static_cast<unsigned>(dpp_i<kMirror>(static_cast<int>(x))));
-  x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast15, 0xA>(0, static_cast<int>(x))));
-  x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast31, 0xC>(0, static_cast<int>(x))));
-  return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
 }
 
 // f(integral constants 0 .. N - 1) in order
@@ -99,6 +94,35 @@ struct Grp {
   __device__ static __forceinline__ int lane() { return static_cast<int>(__lane_id()); }
   __device__ static __forceinline__ int gl() { return lane() & (G - 1); }
   __device__ static __forceinline__ int base() { return lane() & ~(G - 1); }
+
+  // the two 16-lane rows of a 32-lane group: the even rows' value on both,
+  // and the odd rows' (v_permlane16_swap, no LDS round trip)
+  __device__ static __forceinline__ void rows_i(int v, int& even, int& odd) {
+    const auto r = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(v), static_cast<unsigned>(v), false, false);
+    even = static_cast<int>(r[0]);
+    odd = static_cast<int>(r[1]);
+  }
+  __device__ static __forceinline__ void rows(double v, double& even, double& odd) {
+    int el, ol, eh, oh;
+    rows_i(__double2loint(v), el, ol);
+    rows_i(__double2hiint(v), eh, oh);
+    even = __hiloint2double(eh, el);
+    odd = __hiloint2double(oh, ol);
+  }
+  // value of v in group lane SRC, known at compile time: a readlane, or DPP
+  // inside the 16-lane row (and the other row's by a row swap)
+  template <int SRC>
+  __device__ static __forceinline__ double bcast_c(double v) {
+    if constexpr (G == 64) {
+      return readlane_d(v, SRC);
+    } else {
+      const double z = row_bcast<SRC & 15>(v);
+      if constexpr (G == 16) return z;
+      double even, odd;
+      rows(z, even, odd);
+      return SRC < 16 ? even : odd;
+    }
+  }
 
   // value of v in group lane src (src equal across the group)
   __device__ static __forceinline__ double bcast(double v, int src) {
@@ -131,7 +155,9 @@ struct Grp {
       x = x + dpp_rows_d<kRowBcast31, 0xC>(0.0, x);   // rows 2, 3: + row 1
       return readlane_d(x, 63);
     } else if constexpr (G == 32) {
-      return (x + __shfl_xor(x, 16, 64)) + (0.0 + 0.0);
+      double even, odd;
+      rows(x, even, odd);
+      return (even + odd) + (0.0 + 0.0);
     } else {
       return (x + 0.0) + (0.0 + 0.0);
     }
@@ -146,7 +172,9 @@ struct Grp {
       x = fmax(x, dpp_rows_d<kRowBcast31, 0xC>(x, x));
       return readlane_d(x, 63);
     } else if constexpr (G == 32) {
-      return fmax(x, __shfl_xor(x, 16, 64));
+      double even, odd;
+      rows(x, even, odd);
+      return fmax(even, odd);
     } else {
       return x;
     }
@@ -161,7 +189,27 @@ struct Grp {
       x = ::min(x, dpp_rows_i<kRowBcast31, 0xC>(x, x));
       return __builtin_amdgcn_readlane(x, 63);
     } else if constexpr (G == 32) {
-      return ::min(x, __shfl_xor(x, 16, 64));
+      int even, odd;
+      rows_i(x, even, odd);
+      return ::min(even, odd);
+    } else {
+      return x;
+    }
+  }
+  // largest of one 32-bit key per lane
+  __device__ static __forceinline__ unsigned max_u32(unsigned x) {
+    x = ::max(x, static_cast<unsigned>(dpp_i<kXor1>(static_cast<int>(x))));
+    x = ::max(x, static_cast<unsigned>(dpp_i<kXor2>(static_cast<int>(x))));
+    x = ::max(x, static_cast<unsigned>(dpp_i<kHalfMirror>(static_cast<int>(x))));
+    x = ::max(x, static_cast<unsigned>(dpp_i<kMirror>(static_cast<int>(x))));
+    if constexpr (G == 64) {
+      x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast15, 0xA>(0, static_cast<int>(x))));
+      x = ::max(x, static_cast<unsigned>(dpp_rows_i<kRowBcast31, 0xC>(0, static_cast<int>(x))));
+      return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
+    } else if constexpr (G == 32) {
+      int even, odd;
+      rows_i(static_cast<int>(x), even, odd);
+      return ::max(static_cast<unsigned>(even), static_cast<unsigned>(odd));
     } else {
       return x;
     }
@@ -209,6 +257,8 @@ __host__ __device__ constexpr int pbuf_doubles(int nn) { return (nn + 2) & ~1; }
 // sides), otherwise in P.
 constexpr int kPanel = 4;
 __host__ __device__ constexpr int lu_rows_doubles(int nn) { return kPanel * ((nn + 15) & ~15); }
+// one pivot row, its reciprocal and its position (several cells per wave)
+__host__ __device__ constexpr int lu_row_doubles(int nn) { return ((nn + 15) & ~15) + 2; }
 // state sizes above 32 assemble rates and Jacobian reaction by reaction
 __host__ __device__ constexpr bool reaction_major(int nn) { return nn > 32; }
 __host__ __device__ constexpr int rbuf_doubles(int nn, int nr) {
@@ -358,10 +408,10 @@ struct Cell {
   // whose order of additions does not depend on the group width.
   static constexpr bool kScatter = reaction_major(NN);
 
-  // Reactions of the reaction-major assembly from the packed records: block
-  // by block of 64, one lane per reaction, in the order of the general records
-  // (rx_scatter below them), with the same operations per reaction. The
-  // records hold what the general words make every lane decode: LDS offsets
+  // Reactions from the packed records: one lane per reaction, in the order of
+  // the general records and with the same operations per reaction. The
+  // reaction-major assembly adds into the species sums and J (as rx_scatter);
+  // smaller sizes keep the rates in RB for the species pass. The records hold what the general words make every lane decode: LDS offsets
   // of the species slots (one register serves C, g, h and the sums, by
   // instruction offsets), factors of the mass-action products without selects
   // on the orders, orders as doubles. Products by orders 1 and 2 are exact, so
@@ -370,7 +420,7 @@ struct Cell {
   template <bool JAC>
   __device__ static __forceinline__ void reactions(const MechArgs& A, const MechLds& L, const CellArea& ca, double T,
                                                    double rT, double lnT, double lnRTp, double Ctot) {
-    const int i = Gp::lane();
+    const int i = Gp::gl(), nr = A.nr;
     const double2* rec = A.rec + i;
     const int N = A.rec_n;
     char* const Cb = reinterpret_cast<char*>(ca.C);
@@ -378,7 +428,7 @@ struct Cell {
     constexpr int kG = 8 * NN, kH = 16 * NN, kOm = 24 * NN, kWT = 32 * NN, kTd = 40 * NN;   // byte offsets from C
     const auto at = [&](unsigned off, int arr) { return *reinterpret_cast<const double*>(Cb + off + arr); };
 #pragma nounroll
-    for (int r0 = 0; r0 < N; r0 += 64, rec += 64) {
+    for (int r0 = 0; r0 < nr; r0 += G, rec += G) {
       const double2 k1 = rec[0], k2 = rec[N], n0 = rec[2 * N], n1 = rec[3 * N];
       const uint4 w0 = reinterpret_cast<const uint4*>(rec)[5 * N];
       const int type = (w0.w >> 8) & 3;
@@ -434,6 +484,19 @@ struct Cell {
         krT = kr * theta;
         q0b = q0 * beta;
         dqdT = theta * (kf * dlnkf * Pf - kr * dlnkr * Pr) + q0 * dthdT;
+      }
+      if constexpr (!kScatter) {
+        const int rx = r0 + i;
+        if (rx < nr) {
+          ca.RB[rx] = q;
+          if (JAC) {
+            ca.RB[nr + rx] = kfT;
+            ca.RB[2 * nr + rx] = krT;
+            ca.RB[3 * nr + rx] = q0b;
+            ca.RB[4 * nr + rx] = dqdT;
+          }
+        }
+        continue;
       }
       // slots f0 f1 f2 p0 p1 p2: species sums, then J by row and column
       const double nu[6] = {-n0.x, -n1.x, -n2.x, n0.y, n1.y, n2.y};
@@ -500,7 +563,68 @@ struct Cell {
     }
   }
 
-  // The same from the general records (any orders).
+  // Production rate and Jacobian row of one species (this lane's) from the
+  // rates in RB, entry by entry of its reaction list: the partial derivatives
+  // by the record's factors, added in the order of the general words. The next
+  // entry's record is fetched before the current one is used.
+  __device__ static __forceinline__ void species_row(const MechArgs& A, const MechLds& L, const CellArea& ca,
+                                                     double* Jrow, int e0, int e1, double& om, double& wT,
+                                                     double& td) {
+    const int nr = A.nr, N = A.rec_n;
+    const char* const Cb = reinterpret_cast<const char*>(ca.C);
+    char* const Jb = reinterpret_cast<char*>(Jrow);
+    const auto at = [&](unsigned off) { return *reinterpret_cast<const double*>(Cb + off); };
+    const auto add = [&](unsigned off, double v) { lds_add(reinterpret_cast<double*>(Jb + off), v); };
+    if (e0 >= e1) return;
+    unsigned ent = L.sp_ent[e0];
+    const double2* rec = A.rec + (ent & 0xfff);
+    uint4 w0 = reinterpret_cast<const uint4*>(rec)[5 * N];
+    double2 n0 = rec[2 * N];
+#pragma nounroll
+    for (int e = e0; e < e1; ++e) {
+      const int rx = ent & 0xfff;
+      const double nu = static_cast<double>(static_cast<int>(ent >> 12) - 8);
+      const uint4 w = w0;
+      const double2 n = n0;
+      const double2* const cur = rec;
+      ent = e + 1 < e1 ? L.sp_ent[e + 1] : ent;
+      rec = A.rec + (ent & 0xfff);
+      w0 = reinterpret_cast<const uint4*>(rec)[5 * N];
+      n0 = rec[2 * N];
+      const unsigned f0 = w.x & 0xffff, f1 = w.x >> 16, p0 = w.y & 0xffff, p1 = w.y >> 16;
+      const double cf0 = at(f0), cp0 = at(p0), cf1 = at(w.z & 0xffff), cp1 = at(w.z >> 16);
+      const double qr = ca.RB[rx], kfT = ca.RB[nr + rx], krT = ca.RB[2 * nr + rx], q0b = ca.RB[3 * nr + rx],
+                   dqdT = ca.RB[4 * nr + rx];
+      om = om + nu * qr;
+      wT = wT + nu * dqdT;
+      const double af = nu * kfT, ar = nu * krT;
+      const int type = (w.w >> 8) & 3;
+      uint4 w1{0, 0, 0, 0};
+      if (type != 0 || (w.w & (4u | 32u | 64u))) w1 = reinterpret_cast<const uint4*>(cur)[6 * N];
+      if (w.w & (4u | 32u | 64u)) {
+        const double cf2 = at(w1.y & 0xffff), cp2 = at(w1.y >> 16);
+        add(f0, af * (n.x * cf1 * cf2));
+        if (w.w & 2u) add(f1, af * (cf0 * cf2));
+        if (w.w & 4u) add(w1.x & 0xffff, af * (cf0 * cf1));
+        add(p0, -(ar * (n.y * cp1 * cp2)));
+        if (w.w & 16u) add(p1, -(ar * (cp0 * cp2)));
+        if (w.w & 32u) add(w1.x >> 16, -(ar * (cp0 * cp1)));
+      } else {
+        add(f0, af * (n.x * cf1));
+        if (w.w & 2u) add(f1, af * cf0);
+        add(p0, -(ar * (n.y * cp1)));
+        if (w.w & 16u) add(p1, -(ar * cp0));
+      }
+      if (type >= 1) {
+        const double ab = nu * q0b;
+        td = td + ab;
+        const int eoff = w1.z & 0xffff, neff = (w1.z >> 16) & 0xff;
+        for (int c = 0; c < neff; ++c) add(8 * L.eff_sp[eoff + c], ab * L.eff_am1[eoff + c]);
+      }
+    }
+  }
+
+  // The reaction-major assembly from the general records (any orders).
   template <bool JAC>
   __device__ static __forceinline__ void reactions_general(const MechArgs& A, const MechLds& L, const CellArea& ca,
                                                            double T, double rT, double lnT, double lnRTp,
@@ -534,11 +658,11 @@ struct Cell {
     const int i = Gp::gl();                 // state component of this lane
     const bool sp = i >= 1 && i <= ns;      // lane holds species i-1
     const int s = sp ? i - 1 : 0;
-    const double T = Gp::bcast(y, 0);
+    const double T = Gp::template bcast_c<0>(y);
     const double rT = 1.0 / T;
     // ln T and ln(RT/p_atm) by one logarithm, on lanes 0 and 1
     const double lns = log(i == 1 ? kR * T / kPatm : T);
-    const double lnT = Gp::bcast(lns, 0), lnRTp = Gp::bcast(lns, 1);
+    const double lnT = Gp::template bcast_c<0>(lns), lnRTp = Gp::template bcast_c<1>(lns);
     // mixture state
     const double Ys = sp ? y : 0.0;
     const double rWs = sp ? L.rW[s] : 0.0;
@@ -598,10 +722,11 @@ struct Cell {
         reactions_general<JAC>(A, L, ca, T, rT, lnT, lnRTp, Ctot);
       }
     } else {
-      for (int r0 = 0; r0 < nr; r0 += G) {
-        const int rx = r0 + i;
-        if (rx >= nr) break;
-        reaction_rate<JAC>(L, ca.C, ca.gRT, ca.hRT, ca.RB, nr, rx, T, rT, lnT, lnRTp, Ctot);
+      if (A.rec) {
+        reactions<JAC>(A, L, ca, T, rT, lnT, lnRTp, Ctot);
+      } else {
+        for (int rx = i; rx < nr; rx += G)
+          reaction_rate<JAC>(L, ca.C, ca.gRT, ca.hRT, ca.RB, nr, rx, T, rT, lnT, lnRTp, Ctot);
       }
     }
     wsync();
@@ -632,6 +757,8 @@ struct Cell {
           const double nu = static_cast<double>(static_cast<int>(ent >> 12) - 8);
           om = om + nu * ca.RB[ent & 0xfff];
         }
+      } else if (A.rec) {
+        species_row(A, L, ca, Jrow, e0, e1, om, wT, td);
       } else {
         unsigned ent = e0 < e1 ? L.sp_ent[e0] : 0u;
         uint4 w = L.rint[ent & 0xfff];
@@ -848,7 +975,7 @@ struct Cell {
     if constexpr (G == 64) {
       return lu_wave(M, pos, rdiag, P, pivk);
     } else {
-      return lu_group(M, pos, rdiag, pivk);
+      return lu_group(M, pos, rdiag, P, pivk);
     }
   }
 
@@ -897,7 +1024,7 @@ struct Cell {
         // ties, zeros and non-finite entries take the exact search
         const unsigned hi = static_cast<unsigned>(__double2hiint(a)) & 0x7fffffffu;
         const unsigned key = pos >= k ? hi : 0u;
-        const unsigned hmax = wave_max_u32(key);
+        const unsigned hmax = Gp::max_u32(key);
         const unsigned long long bal = __ballot(key == hmax);
         int owner = __builtin_ctzll(bal);
         double rp;
@@ -1006,57 +1133,69 @@ struct Cell {
 #undef CHEM_F
   }
 
-  // Several cells per wave: column by column, every pivot-row element by a
-  // lane shuffle.
-  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, int* pivk) {
+  // Several cells per wave: column by column. The pivot row, its reciprocal
+  // and its position go through the group's LDS buffer P to every 16-lane row
+  // (lane l of a row reads columns 16 J + l), and each element's update is one
+  // multiply-add whose pivot-row element is broadcast along the row by DPP: one
+  // LDS round trip a column, where a lane shuffle per element needs two
+  // through the LDS crossbar.
+  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+    constexpr int kRow = (NN + 15) & ~15;    // then the reciprocal and the position
     int info = 0;
     const int i = Gp::gl();
-    pos = i < NN ? i : kBig;
+    pos = i < NN ? i : -1;
     rdiag = 0.0;
-#pragma unroll
-    for (int k = 0; k < NN; ++k) {
+    static_for<NN>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
       const double a = M[k];
-      const bool cand = pos >= k && pos < NN;
-      const double key = cand ? fabs(a) : -1.0;
-      const double amax = Gp::max(key);
-      const bool tie = key == amax;
-      const unsigned long long bal = Gp::ballot(tie);
-      int owner;
-      if (__popcll(bal) == 1) {
-        owner = __ffsll(static_cast<long long>(bal)) - 1;
-      } else {
+      double ra = __builtin_amdgcn_rcp(a);
+      ra = fma(ra, fma(-a, ra, 1.0), ra);
+      ra = fma(ra, fma(-a, ra, 1.0), ra);
+      const unsigned hi = static_cast<unsigned>(__double2hiint(a)) & 0x7fffffffu;
+      const unsigned key = pos >= k ? hi : 0u;
+      const unsigned hmax = Gp::max_u32(key);
+      const unsigned long long bal = Gp::ballot(key == hmax);
+      int owner = __builtin_ctzll(bal);
+      bool zero = false;
+      if (!__all((bal & (bal - 1)) == 0 && hmax < 0x7ff00000u)) {
+        const double dkey = pos >= k ? fabs(a) : -1.0;
+        const double amax = Gp::max(dkey);
+        const bool tie = dkey == amax;
         const int pmin = Gp::min_i(tie ? pos : kBig);
         owner = Gp::first(tie && pos == pmin);
+        zero = amax == 0.0;
       }
-      const int ppos = Gp::bcast_i(pos, owner);
       const bool is_owner = i == owner;
+      wsync();
+      if (is_owner) {
+#pragma unroll
+        for (int j = k + 1; j < NN; ++j) P[j] = M[j];
+        P[kRow] = zero ? 0.0 : ra;
+        P[kRow + 1] = __hiloint2double(0, pos);
+      }
+      wsync();
+      const double rp = P[kRow];
+      const int ppos = __double2loint(P[kRow + 1]);
+      double u[kRow / 16];
+#pragma unroll
+      for (int J = (k + 1) / 16; J < kRow / 16; ++J) u[J] = P[16 * J + (i & 15)];
+      if (zero && info == 0) info = k + 1;
+      if (pivk) pivk[k] = ppos;
+      pos = pos == k ? ppos : pos;
       if (is_owner) {
         pos = k;
-      } else if (pos == k) {
-        pos = ppos;
+        rdiag = rp;
       }
-      if (pivk) pivk[k] = ppos;
-      const double akk = Gp::bcast(a, owner);
-      double rp;
-      if (amax == 0.0) {
-        if (info == 0) info = k + 1;
-        rp = 0.0;
-      } else {
-        // hardware reciprocal refined by two Newton steps (a shorter
-        // dependent chain than a correctly rounded division)
-        rp = __builtin_amdgcn_rcp(akk);
-        rp = fma(rp, fma(-akk, rp, 1.0), rp);
-        rp = fma(rp, fma(-akk, rp, 1.0), rp);
-      }
-      if (is_owner) rdiag = rp;
-      const bool below = pos > k && pos < NN;
+      const bool below = pos > k;
       const double l = below ? a * rp : 0.0;
       if (below) M[k] = l;
-#pragma unroll
-      for (int j = k + 1; j < NN; ++j) M[j] = fma(-l, Gp::bcast(M[j], owner), M[j]);
-    }
+      static_for<NN - 1 - k>([&](auto jc) {
+        constexpr int j = k + 1 + decltype(jc)::value;
+        M[j] = fma(-l, row_bcast<(j & 15)>(u[j / 16]), M[j]);
+      });
+    });
     // rows to the lanes of their positions
-    const int dst = 4 * (Gp::base() + (pos < NN ? pos : i));
+    const int dst = 4 * (Gp::base() + (pos >= 0 ? pos : i));
 #pragma unroll
     for (int j = 0; j < NN; ++j) M[j] = permute_d(M[j], dst);
     rdiag = permute_d(rdiag, dst);
@@ -1079,193 +1218,194 @@ struct Cell {
     // with one cell per wave the comparisons are formed at their use, one
     // instruction each, not hoisted out of the stages (which spilled them)
     if constexpr (G == 64) asm volatile("" : "+v"(i));
-    const bool row = G == 64 ? pos >= 0 : pos < NN;
-    b = permute_d(b, 4 * (Gp::base() + (row ? pos : i)));
+    b = permute_d(b, 4 * (Gp::base() + (pos >= 0 ? pos : i)));
     // the multipliers are masked rather than the update, which keeps the
     // selects off the chain of dependent broadcasts (a zero multiplier
     // leaves b unchanged for finite z)
-#pragma unroll
-    for (int j = 0; j < NN - 1; ++j) {
+    static_for<NN - 1>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
       const double lm = i > j ? M[j] : 0.0;
-      const double z = Gp::bcast(b, j);
-      b = fma(-lm, z, b);
-    }
-#pragma unroll
-    for (int j = NN - 1; j > 0; --j) {
+      b = fma(-lm, Gp::template bcast_c<j>(b), b);
+    });
+    static_for<NN - 1>([&](auto jc) {
+      constexpr int j = NN - 1 - decltype(jc)::value;
       const double um = i < j ? M[j] : 0.0;
-      const double z = Gp::bcast(b * rdiag, j);
-      b = fma(-um, z, b);
-    }
+      b = fma(-um, Gp::template bcast_c<j>(b * rdiag), b);
+    });
     return b * rdiag;
   }
 
   // -------------------------------------------------------------------------
-  // adaptive Rosenbrock integration (scheme SCHEME) over [0, dt] for one cell
-  // (y: this lane's component)
+  // adaptive Rosenbrock integration (scheme SCHEME) over [0, dt] of one cell:
+  // begin(), attempt() until it returns false, then St holds the result
   // -------------------------------------------------------------------------
   // GEN: honour the forward-difference Jacobian and the state without the
   // bath gas (run-time options); without it both are compiled out, so that
   // the kernels of the default options carry none of their code.
-  template <int SCHEME, bool GEN>
-  __device__ static __forceinline__ void integrate(const MechArgs& A, const MechLds& L, const CellArea& ca,
-                                                   int* jlock, const OptsDev& o, double p, double dt,
-                                                   double& y, double& hio, int& nacc_o, int& nrej_o, int& status_o,
-                                                   int& njac_o, int& nfev_o) {
-    using TB = Tab<SCHEME>;
+  struct St {
+    double p, y;                // pressure; this lane's state component
+    double h, hnext, t, f0;     // next substep, proposal, time, f at y
+    int nacc, nrej, att, consec, status;
+    int njac, nfev;             // evaluations of J and of f (a difference Jacobian's included)
+    bool need;                  // J of the current y not yet evaluated
+  };
+
+  // h: first substep (<= 0: dt). Returns whether there is anything to do.
+  template <bool GEN>
+  __device__ static __forceinline__ bool begin(const MechArgs& A, const OptsDev& o, double p, double y, double h,
+                                               double dt, St& c) {
     const int ns = A.ns;
     const bool nb = GEN && o.no_bath != 0;   // bath gas (lane ns) derived, not integrated
+    const bool valid = Gp::gl() < (nb ? ns : ns + 1);
+    if (nb) y = with_bath(ns, y);
+    c = St{p, y, h > 0.0 ? h : dt, 0.0, 0.0, 0.0, 0, 0, 0, 0, 0, 0, 0, true};
+    c.hnext = c.h;
+    // a non-finite state, or a pressure that is not a positive number
+    if (Gp::any((valid && !isfinite(y)) || !isfinite(p) || !(p > 0.0))) c.status = 3;
+    return c.status == 0 && c.t < dt;
+  }
+
+  // One attempted step. Returns whether the integration goes on.
+  template <int SCHEME, bool GEN>
+  __device__ static __forceinline__ bool attempt(const MechArgs& A, const MechLds& L, const CellArea& ca, int* jlock,
+                                                 const OptsDev& o, double dt, St& c) {
+    using TB = Tab<SCHEME>;
+    const int ns = A.ns;
+    const bool nb = GEN && o.no_bath != 0;
     const int n = nb ? ns : ns + 1;       // integrated components
     const int i = Gp::gl();
     const bool valid = i < n;
-    if (nb) y = with_bath(ns, y);
     double M[NN];
     int pos;
     double rdiag;
-    int status = 0;
-    // a non-finite state, or a pressure that is not a positive number
-    if (Gp::any((valid && !isfinite(y)) || !isfinite(p) || !(p > 0.0))) status = 3;
-    double h = hio > 0.0 ? hio : dt;
-    double hnext = h, t = 0.0;
-    int nacc = 0, nrej = 0, att = 0, consec = 0;
-    int njac = 0, nfev = 0;     // evaluations of J and of f (a difference Jacobian's included)
-    bool need = true;
-    double f0 = 0.0;
-    while (status == 0 && t < dt) {
-      if (att >= o.max_steps) {
-        status = 1;
-        break;
-      }
-      if (need) {
-        ++njac;
-        nfev += (GEN && o.jac_fd) ? 1 + n : 1;
-      }
-      const double rem = dt - t;
-      double hc = h;
-      bool clipped = false;
-      if (hc >= rem) {
-        hc = rem;
-        clipped = true;
-      }
-      if (hc < kHMin) {
-        status = 2;
-        break;
-      }
-      const double g = 1.0 / (TB::gamma * hc);
-      if constexpr (kScatter && !GEN) {
-        // f of the step start and M = g I - J, formed together; after a
-        // rejected attempt (a few per cent) J is formed again
-        f0 = eval<true, true>(A, L, ca, p, y, jlock, g, M);
-        need = false;
-      } else {
-        // f and J of the step start. A buffer of the wave's own keeps J
-        // across rejected attempts; a shared one may have been overwritten
-        j_acquire(jlock);
-        if (need || jlock) {
-          if (GEN && o.jac_fd) {
-            f0 = rhs<false>(A, L, ca, p, y);
-            fd_jacobian(A, L, ca, p, y, f0, nb);
-          } else {
-            f0 = rhs<true>(A, L, ca, p, y);
-            if (nb) reduce_bath(ca, ns);
-          }
-          need = false;
-        }
-        if (i < NN) {
-#pragma unroll
-          for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - ca.J[i * NN + j];
-        } else {
-#pragma unroll
-          for (int j = 0; j < NN; ++j) M[j] = 0.0;
-        }
-        j_release(jlock);
-      }
-      const int info = lu(M, pos, rdiag, ca.P, nullptr);
-      ++att;
-      if (info) {
-        status = 4;
-        break;
-      }
-      // stages: one right-hand side and one solve call site for all four;
-      // every sum runs over j < st in ascending order with the scheme's
-      // coefficients, zeros included, as the oracle forms it
-      double u1 = 0.0, u2 = 0.0, u3 = 0.0, u4 = 0.0;
-      double fs = f0;
-#pragma nounroll
-      for (int st = 0; st < 4; ++st) {
-        const int src = tab_fsrc<SCHEME>(st);
-        if (src == kFnew) {
-          double ys = y;
-          if (st > 0) ys = ys + tab_a<SCHEME>(st, 0) * u1;
-          if (st > 1) ys = ys + tab_a<SCHEME>(st, 1) * u2;
-          if (st > 2) ys = ys + tab_a<SCHEME>(st, 2) * u3;
-          if (nb) ys = with_bath(ns, ys);
-          fs = rhs<false>(A, L, ca, p, ys);
-          ++nfev;
-        } else if (src == kFy) {
-          fs = f0;
-        }
-        double v = fs;
-        if (st > 0) v = v + (tab_c<SCHEME>(st, 0) / hc) * u1;
-        if (st > 1) v = v + (tab_c<SCHEME>(st, 1) / hc) * u2;
-        if (st > 2) v = v + (tab_c<SCHEME>(st, 2) / hc) * u3;
-        if (nb && i == ns) v = 0.0;         // the bath lane takes no step of its own
-        const double x = solve(M, pos, rdiag, v);
-        if (st == 0) u1 = x;
-        else if (st == 1) u2 = x;
-        else if (st == 2) u3 = x;
-        else u4 = x;
-      }
-      // new solution and error estimate
-      double yn = y + TB::m[0] * u1;
-      yn = yn + TB::m[1] * u2;
-      yn = yn + TB::m[2] * u3;
-      yn = yn + TB::m[3] * u4;
-      if (nb) yn = with_bath(ns, yn);
-      double ev = 0.0 + TB::e[0] * u1;
-      ev = ev + TB::e[1] * u2;
-      ev = ev + TB::e[2] * u3;
-      ev = ev + TB::e[3] * u4;
-      const double sc = o.atol + o.rtol * fmax(fabs(y), fabs(yn));
-      const double q = ev / sc;
-      const double acc = Gp::sum(valid ? q * q : 0.0);
-      double err = sqrt(acc / n);
-      double hnew;
-      if (Gp::any(valid && !isfinite(yn)) || !isfinite(err)) {
-        err = INFINITY;
-        hnew = hc * kFacRej;
-      } else {
-        double fac = step_factor<SCHEME>(err);
-        fac = fmin(kFacMax, fmax(kFacMin, fac));
-        hnew = hc * fac;
-      }
-      if (err <= 1.0) {
-        if (consec > 0) hnew = fmin(hnew, hc);
-        const double Tn = Gp::bcast(yn, 0);
-        if (!(Tn >= kTMin && Tn <= kTMax)) {
-          status = 5;
-          break;
-        }
-        y = yn;
-        ++nacc;
-        t = clipped ? dt : t + hc;
-        hnext = clipped ? fmax(hnew, h) : hnew;
-        h = hnew;
-        consec = 0;
-        need = true;
-      } else {
-        ++nrej;
-        ++consec;
-        if (consec >= 2) hnew = hc * kFacRej;
-        h = hnew;
-      }
+    if (c.att >= o.max_steps) {
+      c.status = 1;
+      return false;
     }
-    if (status != 0) hnext = h;
-    hio = hnext;
-    nacc_o = nacc;
-    nrej_o = nrej;
-    status_o = status;
-    njac_o = njac;
-    nfev_o = nfev;
+    if (c.need) {
+      ++c.njac;
+      c.nfev += (GEN && o.jac_fd) ? 1 + n : 1;
+    }
+    const double rem = dt - c.t;
+    double hc = c.h;
+    bool clipped = false;
+    if (hc >= rem) {
+      hc = rem;
+      clipped = true;
+    }
+    if (hc < kHMin) {
+      c.status = 2;
+      return false;
+    }
+    const double g = 1.0 / (TB::gamma * hc);
+    if constexpr (kScatter && !GEN) {
+      // f of the step start and M = g I - J, formed together; after a
+      // rejected attempt (a few per cent) J is formed again
+      c.f0 = eval<true, true>(A, L, ca, c.p, c.y, jlock, g, M);
+      c.need = false;
+    } else {
+      // f and J of the step start. A buffer of the wave's own keeps J
+      // across rejected attempts; a shared one may have been overwritten
+      j_acquire(jlock);
+      if (c.need || jlock) {
+        if (GEN && o.jac_fd) {
+          c.f0 = rhs<false>(A, L, ca, c.p, c.y);
+          fd_jacobian(A, L, ca, c.p, c.y, c.f0, nb);
+        } else {
+          c.f0 = rhs<true>(A, L, ca, c.p, c.y);
+          if (nb) reduce_bath(ca, ns);
+        }
+        c.need = false;
+      }
+      if (i < NN) {
+#pragma unroll
+        for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - ca.J[i * NN + j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < NN; ++j) M[j] = 0.0;
+      }
+      j_release(jlock);
+    }
+    const int info = lu(M, pos, rdiag, ca.P, nullptr);
+    ++c.att;
+    if (info) {
+      c.status = 4;
+      return false;
+    }
+    // stages: one right-hand side and one solve call site for all four;
+    // every sum runs over j < st in ascending order with the scheme's
+    // coefficients, zeros included, as the oracle forms it
+    double u1 = 0.0, u2 = 0.0, u3 = 0.0, u4 = 0.0;
+    double fs = c.f0;
+#pragma nounroll
+    for (int st = 0; st < 4; ++st) {
+      const int src = tab_fsrc<SCHEME>(st);
+      if (src == kFnew) {
+        double ys = c.y;
+        if (st > 0) ys = ys + tab_a<SCHEME>(st, 0) * u1;
+        if (st > 1) ys = ys + tab_a<SCHEME>(st, 1) * u2;
+        if (st > 2) ys = ys + tab_a<SCHEME>(st, 2) * u3;
+        if (nb) ys = with_bath(ns, ys);
+        fs = rhs<false>(A, L, ca, c.p, ys);
+        ++c.nfev;
+      } else if (src == kFy) {
+        fs = c.f0;
+      }
+      double v = fs;
+      if (st > 0) v = v + (tab_c<SCHEME>(st, 0) / hc) * u1;
+      if (st > 1) v = v + (tab_c<SCHEME>(st, 1) / hc) * u2;
+      if (st > 2) v = v + (tab_c<SCHEME>(st, 2) / hc) * u3;
+      if (nb && i == ns) v = 0.0;         // the bath lane takes no step of its own
+      const double x = solve(M, pos, rdiag, v);
+      if (st == 0) u1 = x;
+      else if (st == 1) u2 = x;
+      else if (st == 2) u3 = x;
+      else u4 = x;
+    }
+    // new solution and error estimate
+    double yn = c.y + TB::m[0] * u1;
+    yn = yn + TB::m[1] * u2;
+    yn = yn + TB::m[2] * u3;
+    yn = yn + TB::m[3] * u4;
+    if (nb) yn = with_bath(ns, yn);
+    double ev = 0.0 + TB::e[0] * u1;
+    ev = ev + TB::e[1] * u2;
+    ev = ev + TB::e[2] * u3;
+    ev = ev + TB::e[3] * u4;
+    const double sc = o.atol + o.rtol * fmax(fabs(c.y), fabs(yn));
+    const double q = ev / sc;
+    const double acc = Gp::sum(valid ? q * q : 0.0);
+    double err = sqrt(acc / n);
+    double hnew;
+    if (Gp::any(valid && !isfinite(yn)) || !isfinite(err)) {
+      err = INFINITY;
+      hnew = hc * kFacRej;
+    } else {
+      double fac = step_factor<SCHEME>(err);
+      fac = fmin(kFacMax, fmax(kFacMin, fac));
+      hnew = hc * fac;
+    }
+    if (err <= 1.0) {
+      if (c.consec > 0) hnew = fmin(hnew, hc);
+      const double Tn = Gp::template bcast_c<0>(yn);
+      if (!(Tn >= kTMin && Tn <= kTMax)) {
+        c.status = 5;
+        return false;
+      }
+      c.y = yn;
+      ++c.nacc;
+      c.t = clipped ? dt : c.t + hc;
+      c.hnext = clipped ? fmax(hnew, c.h) : hnew;
+      c.h = hnew;
+      c.consec = 0;
+      c.need = true;
+    } else {
+      ++c.nrej;
+      ++c.consec;
+      if (c.consec >= 2) hnew = hc * kFacRej;
+      c.h = hnew;
+    }
+    return c.t < dt;
   }
 };
 
@@ -1286,42 +1426,45 @@ __device__ __forceinline__ void cell_features(int ns, double y, double p, double
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
-template <int NN, int G, int SCHEME, bool GEN>
-__device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& L, const CellArea& ca, int* jlock,
-                                         long long cell) {
-  using C = Cell<NN, G>;
+// Read one cell and begin its integration; store its result.
+template <int NN, int G, bool GEN>
+__device__ __forceinline__ bool load_cell(const IntegrateArgs& a, long long cell, typename Cell<NN, G>::St& c,
+                                          float (&ft)[4]) {
   const int ns = a.m.ns;
-  const int w2 = ns + 2;
   const int i = Grp<G>::gl();
-  const double* pin = a.phi_in + cell * w2;
+  const double* pin = a.phi_in + cell * (ns + 2);
   const double p = pin[1];
-  double y = i == 0 ? pin[0] : (i <= ns ? pin[1 + i] : 0.0);
-  float ft[4];
+  const double y = i == 0 ? pin[0] : (i <= ns ? pin[1 + i] : 0.0);
   if (a.log.cap > 0) cell_features<G>(ns, y, p, a.dt, ft);
-  double h = a.h_io ? a.h_io[cell] : 0.0;
-  int nacc, nrej, st, njac, nfev;
-  C::template integrate<SCHEME, GEN>(a.m, L, ca, jlock, a.o, p, a.dt, y, h, nacc, nrej, st, njac, nfev);
-  double* pout = a.phi_out + cell * w2;
+  return Cell<NN, G>::template begin<GEN>(a.m, a.o, p, y, a.h_io ? a.h_io[cell] : 0.0, a.dt, c);
+}
+
+template <int NN, int G>
+__device__ __forceinline__ void store_cell(const IntegrateArgs& a, long long cell,
+                                           const typename Cell<NN, G>::St& c, const float (&ft)[4]) {
+  const int ns = a.m.ns;
+  const int i = Grp<G>::gl();
+  double* pout = a.phi_out + cell * (ns + 2);
   if (i == 0) {
-    pout[0] = y;
-    pout[1] = p;
+    pout[0] = c.y;
+    pout[1] = c.p;
   } else if (i <= ns) {
-    pout[1 + i] = y;
+    pout[1 + i] = c.y;
   }
   if (i == 0) {
-    if (a.h_io) a.h_io[cell] = h;
+    if (a.h_io) a.h_io[cell] = c.status != 0 ? c.h : c.hnext;
     if (a.accumulate) {
-      if (a.n_acc) a.n_acc[cell] += nacc;
-      if (a.n_rej) a.n_rej[cell] += nrej;
-      if (a.status && a.status[cell] == 0) a.status[cell] = static_cast<signed char>(st);
-      if (a.n_jac) a.n_jac[cell] += njac;
-      if (a.n_fev) a.n_fev[cell] += nfev;
+      if (a.n_acc) a.n_acc[cell] += c.nacc;
+      if (a.n_rej) a.n_rej[cell] += c.nrej;
+      if (a.status && a.status[cell] == 0) a.status[cell] = static_cast<signed char>(c.status);
+      if (a.n_jac) a.n_jac[cell] += c.njac;
+      if (a.n_fev) a.n_fev[cell] += c.nfev;
     } else {
-      if (a.n_acc) a.n_acc[cell] = nacc;
-      if (a.n_rej) a.n_rej[cell] = nrej;
-      if (a.status) a.status[cell] = static_cast<signed char>(st);
-      if (a.n_jac) a.n_jac[cell] = njac;
-      if (a.n_fev) a.n_fev[cell] = nfev;
+      if (a.n_acc) a.n_acc[cell] = c.nacc;
+      if (a.n_rej) a.n_rej[cell] = c.nrej;
+      if (a.status) a.status[cell] = static_cast<signed char>(c.status);
+      if (a.n_jac) a.n_jac[cell] = c.njac;
+      if (a.n_fev) a.n_fev[cell] = c.nfev;
     }
     if (a.log.cap > 0) {
       const unsigned long long k = atomicAdd(a.log.head, 1ull) % static_cast<unsigned long long>(a.log.cap);
@@ -1329,9 +1472,30 @@ __device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& 
       a.log.feats[4 * k + 1] = ft[1];
       a.log.feats[4 * k + 2] = ft[2];
       a.log.feats[4 * k + 3] = ft[3];
-      a.log.target[k] = logf(static_cast<float>(nacc + nrej > 0 ? nacc + nrej : 1));
+      a.log.target[k] = logf(static_cast<float>(c.nacc + c.nrej > 0 ? c.nacc + c.nrej : 1));
     }
   }
+}
+
+template <int NN, int G, int SCHEME, bool GEN>
+__device__ __forceinline__ void run_cell(const IntegrateArgs& a, const MechLds& L, const CellArea& ca, int* jlock,
+                                         long long cell) {
+  typename Cell<NN, G>::St c;
+  float ft[4];
+  bool go = load_cell<NN, G, GEN>(a, cell, c, ft);
+  while (go) go = Cell<NN, G>::template attempt<SCHEME, GEN>(a.m, L, ca, jlock, a.o, a.dt, c);
+  store_cell<NN, G>(a, cell, c, ft);
+}
+
+// the next run of a.chunk queue positions for this group
+template <int G>
+__device__ __forceinline__ bool pull(const IntegrateArgs& a, long long& q, long long& end) {
+  unsigned long long idx = 0;
+  if (Grp<G>::gl() == 0) idx = atomicAdd(a.head, static_cast<unsigned long long>(a.chunk));
+  idx = static_cast<unsigned long long>(__shfl(static_cast<long long>(idx), Grp<G>::base(), 64));
+  q = static_cast<long long>(idx);
+  end = min(q + a.chunk, a.n);
+  return idx < static_cast<unsigned long long>(a.n);
 }
 
 // Waves per SIMD that the register allocator plans for: two where pairs of
@@ -1364,16 +1528,30 @@ k_integrate(IntegrateArgs a) {
   if (!PERSIST) {
     const long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
     if (cell < a.n) run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, cell);
+  } else if constexpr (G == 64) {
+    long long q, end;
+    while (pull<G>(a, q, end))
+      for (; q < end; ++q)
+        run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, a.perm ? static_cast<long long>(a.perm[q]) : q);
   } else {
+    // Several cells per wave: a group that finishes its cell takes the next
+    // one while the others go on, so the groups attempt steps together until
+    // the queue is empty, not until the longest of each set of cells ends.
+    typename Cell<NN, G>::St c;
+    float ft[4];
+    long long q = 0, end = 0, cell = 0;
+    bool busy = false;
     for (;;) {
-      unsigned long long idx = 0;
-      if (Grp<G>::gl() == 0) idx = atomicAdd(a.head, static_cast<unsigned long long>(a.chunk));
-      idx = static_cast<unsigned long long>(__shfl(static_cast<long long>(idx), Grp<G>::base(), 64));
-      if (idx >= static_cast<unsigned long long>(a.n)) break;
-      const long long end = min(static_cast<long long>(idx) + a.chunk, a.n);
-      for (long long q = static_cast<long long>(idx); q < end; ++q) {
-        const long long cell = a.perm ? static_cast<long long>(a.perm[q]) : q;
-        run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, cell);
+      if (!busy) {
+        if (q >= end && !pull<G>(a, q, end)) break;
+        cell = a.perm ? static_cast<long long>(a.perm[q]) : q;
+        ++q;
+        busy = load_cell<NN, G, GEN>(a, cell, c, ft);
+        if (!busy) store_cell<NN, G>(a, cell, c, ft);
+      }
+      if (busy) {
+        busy = Cell<NN, G>::template attempt<SCHEME, GEN>(a.m, L, ca, jlock, a.o, a.dt, c);
+        if (!busy) store_cell<NN, G>(a, cell, c, ft);
       }
     }
   }
@@ -1414,7 +1592,7 @@ __global__ void __launch_bounds__(256) k_lu(LuArgs a) {
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* P = reinterpret_cast<double*>(smem) + (wave * CPW + grp) * (G == 64 ? lu_rows_doubles(NN) : 2);
+  double* P = reinterpret_cast<double*>(smem) + (wave * CPW + grp) * (G == 64 ? lu_rows_doubles(NN) : lu_row_doubles(NN));
   const long long m = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
   if (m >= a.batch) return;
   const int n = a.n;
@@ -1559,7 +1737,7 @@ hipError_t launch_lu(const Variant& v, int grid, const LuArgs& a, hipStream_t st
   if (!fn) return hipErrorInvalidValue;
   LuArgs copy = a;
   void* args[] = {&copy};
-  const size_t lds = sizeof(double) * (v.g == 64 ? lu_rows_doubles(v.nn) : 2) * a.wpb * (64 / v.g);
+  const size_t lds = sizeof(double) * (v.g == 64 ? lu_rows_doubles(v.nn) : lu_row_doubles(v.nn)) * a.wpb * (64 / v.g);
   return hipLaunchKernel(fn, dim3(grid), dim3(64 * a.wpb), args, lds, st);
 }
 

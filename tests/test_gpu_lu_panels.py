@@ -1,8 +1,9 @@
 """The one-cell-per-wave LU works in panels of four columns: its pivot search
 orders candidates by their high words and falls back to an exact search, and
 its trailing updates run as broadcast multiply-adds per tile of 16 columns.
-Sizes at the edges of panels and tiles (10, 41, 55, 64), each against the
-oracle's LU:
+With several cells per wave the LU goes column by column, the pivot row
+through LDS. Sizes at the edges of panels and tiles (10, 41, 55, 64; several
+cells per wave 10, 13, 16, 26, 32), each against the oracle's LU:
 
 * integer matrices A = L U with L's entries +-1 and U's diagonal +-2^k, so
   that every column ties (the pivot is the first row) and every operation is
@@ -21,15 +22,16 @@ from paper_2112_05834_amd import chem, synth
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-SIZES = {10: (9, 20, 4, 0, 9, False, 1), 41: (40, 160, 20, 6, 1040, True, 0), 55: (54, 269, 40, 12, 54, True, 0),
+SIZES = {10: (9, 20, 4, 0, 9, False, 1), "10 by 4": (9, 20, 4, 0, 9, False, 4), 13: (12, 36, 4, 2, 1012, True, 4),
+         16: (15, 45, 5, 2, 1015, True, 4), 26: (25, 90, 10, 3, 1025, True, 2), 32: (31, 110, 12, 4, 1031, True, 2), 41: (40, 160, 20, 6, 1040, True, 0), 55: (54, 269, 40, 12, 54, True, 0),
          64: (63, 250, 30, 8, 1063, True, 0)}
 
 
 def _solver(n, tmp_path):
     ns, nr, n3, nt, seed, by_class, cpw = SIZES[n]
     mech = synth.generate_mechanism(ns, nr, n3, nt, seed, ea_by_class=by_class)
-    path = synth.write_mech(mech, str(tmp_path / ("m%d.mech" % n)))
-    return chem.Solver(chem.Mechanism(path), chem.default_opts(cells_per_wave=cpw), device=0)
+    path = synth.write_mech(mech, str(tmp_path / "m.mech"))
+    return chem.Solver(chem.Mechanism(path), chem.default_opts(cells_per_wave=cpw), device=0), ns + 1
 
 
 def _lu(S, A, b=None):
@@ -38,9 +40,9 @@ def _lu(S, A, b=None):
     return [None if t is None else t.cpu().numpy() for t in r]
 
 
-@pytest.mark.parametrize("n", sorted(SIZES))
+@pytest.mark.parametrize("n", list(SIZES))
 def test_lu_ties_and_special_columns(n, tmp_path):
-    S = _solver(n, tmp_path)
+    S, n = _solver(n, tmp_path)
     rng = np.random.Generator(np.random.PCG64(n))
     A = np.zeros((12, n, n))
     for c in range(6):                              # every column ties, exact arithmetic
@@ -70,10 +72,10 @@ def test_lu_ties_and_special_columns(n, tmp_path):
     assert info[11] == n // 2 + 1
 
 
-@pytest.mark.parametrize("n", sorted(SIZES))
+@pytest.mark.parametrize("n", list(SIZES))
 def test_lu_batch_remainders(n, tmp_path):
     """Batches that leave a block's last waves without a matrix."""
-    S = _solver(n, tmp_path)
+    S, n = _solver(n, tmp_path)
     rng = np.random.Generator(np.random.PCG64(100 + n))
     A = rng.normal(size=(13, n, n)) + 3.0 * np.eye(n)[None]
     b = rng.normal(size=(13, n))
