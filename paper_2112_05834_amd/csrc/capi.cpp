@@ -391,8 +391,7 @@ struct Shape {
   chemk::Variant v;
   int wpb = 4;
   int cpw = 1;
-  size_t lds = 0;          // bytes per block of the integration kernel
-  size_t lds_own = 0;      // the same with a Jacobian buffer per cell (evaluation kernel)
+  size_t lds = 0;          // bytes per block
   bool share_j = false;
 };
 
@@ -424,7 +423,7 @@ int pick_shape(const chem_solver* s, const chem_opts& o, int64_t n, Shape& sh) {
     sh.v = s->variants[0];
     sh.cpw = 1;
     sh.wpb = chemk::kWideThreads / 64;
-    sh.lds = sh.lds_own = s->wide_lds;
+    sh.lds = s->wide_lds;
     return CHEM_OK;
   }
   // variant by requested cells per wave, else the first compiled one, or one
@@ -450,11 +449,11 @@ int pick_shape(const chem_solver* s, const chem_opts& o, int64_t n, Shape& sh) {
   const int blob = s->margs.lds_bytes;
   int wpb = o.waves_per_block > 0 ? o.waves_per_block : auto_wpb(s, o, n, sh.v);
   while (wpb > 1 && chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, false) > kMaxLds) --wpb;
-  sh.lds_own = chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, false);
-  if (sh.lds_own > kMaxLds)
+  sh.lds = chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, false);
+  if (sh.lds > kMaxLds)
     return fail(CHEM_EUNSUPPORTED, "mechanism and one cell's work area exceed the 160 KB LDS");
   sh.share_j = chemk::share_j(sh.v, s->nr, s->ns, blob, wpb, kMaxLds);
-  sh.lds = sh.share_j ? chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, true) : sh.lds_own;
+  if (sh.share_j) sh.lds = chemk::block_lds(sh.v, s->nr, s->ns, blob, wpb, true);
   sh.wpb = wpb;
   return CHEM_OK;
 }
@@ -768,8 +767,9 @@ int chem_eval_rhs_jac(chem_solver* s, int64_t n, const double* phi, double* f, d
   if (n == 0) return CHEM_OK;
   DeviceGuard g(s->dev);
   chem_opts o = s->opts;
+  o.schedule = CHEM_PERSISTENT;      // waves take one cell after another here too
   Shape sh;
-  if (int rc = pick_shape(s, o, 0, sh)) return rc;
+  if (int rc = pick_shape(s, o, n, sh)) return rc;
   chemk::EvalArgs a{};
   a.m = s->margs;
   a.n = n;
@@ -787,9 +787,13 @@ int chem_eval_rhs_jac(chem_solver* s, int64_t n, const double* phi, double* f, d
     return CHEM_OK;
   }
   a.cell_doubles = chemk::cell_doubles(sh.v.nn, s->nr, s->ns);
+  a.share_j = sh.share_j ? 1 : 0;
   const long long per_block = static_cast<long long>(sh.wpb) * sh.cpw;
-  const long long grid = (n + per_block - 1) / per_block;
-  HIP_TRY(chemk::launch_eval(sh.v, static_cast<int>(grid), a, sh.lds_own, static_cast<hipStream_t>(stream)), "eval launch");
+  // blocks stay and take further cells, so that the mechanism image is staged
+  // once: as many as fit a CU by their LDS, at most twelve waves
+  const long long resident = std::max<long long>(1, std::min<long long>(kMaxLds / sh.lds, 12 / sh.wpb)) * s->cus;
+  const long long grid = std::min((n + per_block - 1) / per_block, resident);
+  HIP_TRY(chemk::launch_eval(sh.v, static_cast<int>(grid), a, sh.lds, static_cast<hipStream_t>(stream)), "eval launch");
   return CHEM_OK;
 }
 

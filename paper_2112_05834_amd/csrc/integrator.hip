@@ -378,7 +378,8 @@ __device__ __forceinline__ void rx_scatter(const MechLds& L, const double* C, co
 // two waves take turns with one. That halves the largest part of a cell's LDS
 // and lets two waves run on every SIMD. The lock is a word of LDS (NULL: the
 // buffer is the wave's own); a holder never waits for anything while it holds
-// it, and gives it back on every path, so each wait ends.
+// it, and gives it back on every path, so each wait ends. Both fences are for
+// LDS only: a wave's global stores in flight need not end first.
 __device__ __forceinline__ void j_acquire(int* lock) {
   if (!lock) return;
   for (;;) {
@@ -387,11 +388,11 @@ __device__ __forceinline__ void j_acquire(int* lock) {
     if (__builtin_amdgcn_readfirstlane(held) == 0) break;
     __builtin_amdgcn_s_sleep(8);
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 __device__ __forceinline__ void j_release(int* lock) {
   if (!lock) return;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   if (__lane_id() == 0) __hip_atomic_store(lock, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -642,13 +643,13 @@ struct Cell {
   // f = dy/dt at y (this lane's component); with JAC also the analytical
   // Jacobian df/dy: written row-major into ca.J (complete on return), or with
   // TOM straight into M = g I - J, this lane's row in registers. jlock guards
-  // a shared ca.J; with TOM it is held from the first write of ca.J until M is
-  // formed.
+  // a shared ca.J: it is taken before the first write of ca.J, and given back
+  // once M is formed, or (without TOM) by the caller.
   template <bool JAC>
   __device__ static __forceinline__ double rhs(const MechArgs& A, const MechLds& L, const CellArea& ca, double p,
-                                               double y) {
+                                               double y, int* jlock = nullptr) {
     double none[NN];
-    return eval<JAC, false>(A, L, ca, p, y, nullptr, 0.0, none);
+    return eval<JAC, false>(A, L, ca, p, y, jlock, 0.0, none);
   }
 
   template <bool JAC, bool TOM>
@@ -701,7 +702,7 @@ struct Cell {
     }
     if (JAC) {
       dcp = Gp::sum(Ys * dcpR * kR * rWs);
-      if (TOM) j_acquire(jlock);
+      j_acquire(jlock);
       if constexpr (kScatter) {
         double2* z = reinterpret_cast<double2*>(ca.J);
 #pragma unroll
@@ -969,13 +970,14 @@ struct Cell {
   // so on return lane k holds row k of the packed factors (L left of the
   // diagonal, unit diagonal implied; U from the diagonal on) and rdiag =
   // 1/U_kk; pos keeps the position this lane's original row went to (used to
-  // permute right-hand sides). Returns the first singular column + 1.
+  // permute right-hand sides). With piv, lane k also receives the position
+  // interchanged with k. Returns the first singular column + 1.
   // -------------------------------------------------------------------------
-  __device__ static __forceinline__ int lu(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+  __device__ static __forceinline__ int lu(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
     if constexpr (G == 64) {
-      return lu_wave(M, pos, rdiag, P, pivk);
+      return lu_wave(M, pos, rdiag, P, piv);
     } else {
-      return lu_group(M, pos, rdiag, P, pivk);
+      return lu_group(M, pos, rdiag, P, piv);
     }
   }
 
@@ -1000,7 +1002,7 @@ struct Cell {
     return (__ffsll(static_cast<long long>(__ballot(tie && pos == pmin))) - 1) & 63;
   }
 
-  __device__ static __forceinline__ int lu_wave(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+  __device__ static __forceinline__ int lu_wave(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
     unsigned long long zeros = 0;              // columns without a nonzero candidate
     const int i = Gp::lane();
     pos = i < NN ? i : -1;
@@ -1043,7 +1045,7 @@ struct Cell {
         const int ppos = __builtin_amdgcn_readlane(pos, owner);
         pos = pos == k ? ppos : pos;
         pos = i == owner ? k : pos;
-        if (pivk) pivk[k] = ppos;
+        if (piv) *piv = i == k ? ppos : *piv;
         rdiag = i == k ? rp : rdiag;
         const bool below = pos > k;
         const double l = below ? a * rp : 0.0;
@@ -1139,7 +1141,7 @@ struct Cell {
   // multiply-add whose pivot-row element is broadcast along the row by DPP: one
   // LDS round trip a column, where a lane shuffle per element needs two
   // through the LDS crossbar.
-  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, double* P, int* pivk) {
+  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
     constexpr int kRow = (NN + 15) & ~15;    // then the reciprocal and the position
     int info = 0;
     const int i = Gp::gl();
@@ -1180,15 +1182,15 @@ struct Cell {
 #pragma unroll
       for (int J = (k + 1) / 16; J < kRow / 16; ++J) u[J] = P[16 * J + (i & 15)];
       if (zero && info == 0) info = k + 1;
-      if (pivk) pivk[k] = ppos;
+      if (piv) *piv = i == k ? ppos : *piv;
       pos = pos == k ? ppos : pos;
-      if (is_owner) {
-        pos = k;
-        rdiag = rp;
-      }
+      pos = is_owner ? k : pos;
+      rdiag = is_owner ? rp : rdiag;
       const bool below = pos > k;
-      const double l = below ? a * rp : 0.0;
-      if (below) M[k] = l;
+      double l = below ? a * rp : 0.0;
+      M[k] = below ? l : a;
+      // formed here, not carried along as masks and products
+      asm volatile("" : "+v"(M[k]), "+v"(rdiag), "+v"(l), "+v"(pos));
       static_for<NN - 1 - k>([&](auto jc) {
         constexpr int j = k + 1 + decltype(jc)::value;
         M[j] = fma(-l, row_bcast<(j & 15)>(u[j / 16]), M[j]);
@@ -1506,6 +1508,28 @@ constexpr int min_waves_per_eu() { return can_share_j(NN) ? 2 : 1; }
 template <int NN>
 constexpr int max_waves_per_eu() { return NN >= 32 && !can_share_j(NN) ? 1 : 2; }
 
+// Divide a block's LDS: this wave's (group's) areas, the lock of its Jacobian
+// buffer (NULL: the buffer is its own), and the mechanism image staged.
+template <int NN, int G>
+__device__ __forceinline__ CellArea block_area(unsigned char* smem, const MechArgs& m, int wpb, int cell_doubles,
+                                               int share, int*& jlock) {
+  constexpr int CPW = 64 / G;
+  const int wave = threadIdx.x / 64;
+  const int grp = (threadIdx.x % 64) / G;
+  double* const work = reinterpret_cast<double*>(smem + m.lds_bytes);
+  const bool sh = can_share_j(NN) && share;
+  const int nj = sh ? (wpb + 1) / 2 : wpb * CPW;     // Jacobian buffers
+  const int jb = sh ? wave / 2 : wave * CPW + grp;
+  double* const cells = work + nj * j_doubles_c(NN);
+  jlock = nullptr;
+  if (sh) {
+    jlock = reinterpret_cast<int*>(cells + wpb * cell_doubles) + jb;
+    if (threadIdx.x % 128 == 0) *jlock = 0;
+  }
+  stage_mech(smem, m);        // ends in a barrier
+  return cell_area<NN>(work + jb * j_doubles_c(NN), cells + (wave * CPW + grp) * cell_doubles, m.nr);
+}
+
 template <int NN, int G, bool PERSIST, int SCHEME, bool GEN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<NN>(), max_waves_per_eu<NN>())))
 k_integrate(IntegrateArgs a) {
@@ -1513,18 +1537,9 @@ k_integrate(IntegrateArgs a) {
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* const work = reinterpret_cast<double*>(smem + a.m.lds_bytes);
-  const int nj = can_share_j(NN) && a.share_j ? (a.wpb + 1) / 2 : a.wpb * CPW;     // Jacobian buffers
-  const int jb = can_share_j(NN) && a.share_j ? wave / 2 : wave * CPW + grp;
-  double* const cells = work + nj * j_doubles_c(NN);
-  int* jlock = nullptr;
-  if (can_share_j(NN) && a.share_j) {
-    jlock = reinterpret_cast<int*>(cells + a.wpb * a.cell_doubles) + jb;
-    if (threadIdx.x % 128 == 0) *jlock = 0;
-  }
-  stage_mech(smem, a.m);        // ends in a barrier
+  int* jlock;
+  const CellArea ca = block_area<NN, G>(smem, a.m, a.wpb, a.cell_doubles, a.share_j, jlock);
   const MechLds L = mech_views(smem, a.m);
-  const CellArea ca = cell_area<NN>(work + jb * j_doubles_c(NN), cells + (wave * CPW + grp) * a.cell_doubles, a.m.nr);
   if (!PERSIST) {
     const long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
     if (cell < a.n) run_cell<NN, G, SCHEME, GEN>(a, L, ca, jlock, cell);
@@ -1557,65 +1572,119 @@ k_integrate(IntegrateArgs a) {
   }
 }
 
+// Right-hand side and Jacobian of every cell. Rows of J leave LDS one per
+// store, coalesced (each lane a column); with every lane storing its own row
+// a store touched 55 lines for 8 bytes each (8192 54-species cells: 242 us).
 template <int NN, int G>
-__global__ void __launch_bounds__(256) k_eval(EvalArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<NN>()))) k_eval(EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  stage_mech(smem, a.m);
-  const MechLds L = mech_views(smem, a.m);
   using C = Cell<NN, G>;
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
   const int grp = (threadIdx.x % 64) / G;
-  double* const work = reinterpret_cast<double*>(smem + a.m.lds_bytes);
-  const int own = wave * CPW + grp;
-  const CellArea ca = cell_area<NN>(work + own * j_doubles_c(NN),
-                                    work + a.wpb * CPW * j_doubles_c(NN) + own * a.cell_doubles, a.m.nr);
-  const long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
-  if (cell >= a.n) return;
+  int* jlock;
+  const CellArea ca = block_area<NN, G>(smem, a.m, a.wpb, a.cell_doubles, a.share_j, jlock);
+  const MechLds L = mech_views(smem, a.m);
   const int ns = a.m.ns, n = ns + 1;
   const int i = Grp<G>::gl();
-  const double* pin = a.phi + cell * (ns + 2);
-  const double p = pin[1];
-  const double y = i == 0 ? pin[0] : (i <= ns ? pin[1 + i] : 0.0);
-  const double f = a.J ? C::template rhs<true>(a.m, L, ca, p, y) : C::template rhs<false>(a.m, L, ca, p, y);
-  if (i < n) {
-    a.f[cell * n + i] = f;
-    if (a.J)
-      for (int j = 0; j < n; ++j) a.J[(cell * n + i) * n + j] = ca.J[i * NN + j];
+  const long long stride = static_cast<long long>(gridDim.x) * a.wpb * CPW;
+  for (long long cell = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp; cell < a.n; cell += stride) {
+    const double* pin = a.phi + cell * (ns + 2);
+    const double p = pin[1];
+    const double y = i == 0 ? pin[0] : (i <= ns ? pin[1 + i] : 0.0);
+    const double f = a.J ? C::template rhs<true>(a.m, L, ca, p, y, jlock) : C::template rhs<false>(a.m, L, ca, p, y);
+    if (i < n) {
+      a.f[cell * n + i] = f;
+      if (a.J) {
+        double* out = a.J + cell * n * n + i;
+#pragma unroll 8
+        for (int r = 0; r < n; ++r) out[r * n] = ca.J[r * NN + i];
+      }
+    }
+    if (a.J) j_release(jlock);
+    wsync();
   }
 }
 
+// Batched LU. The matrices pass through LDS in runs of whole rows (of all the
+// wave's matrices when it has several), so that global accesses are contiguous
+// over the lanes; each lane then has its row. With every lane loading its own
+// row, 16384 55 x 55 matrices took 826 us, the copy of A they are made in
+// included.
+constexpr int kLuRows = 28;          // rows per run (one matrix per wave)
+__host__ __device__ constexpr int lu_stage_doubles(int nn, int g) {
+  const int stage = (g == 64 ? (nn < kLuRows ? nn : kLuRows) * nn : 64 / g * nn * nn);
+  const int rows = g == 64 ? lu_rows_doubles(nn) : 64 / g * lu_row_doubles(nn);
+  return ((stage > rows ? stage : rows) + 1) & ~1;
+}
+
 template <int NN, int G>
-__global__ void __launch_bounds__(256) k_lu(LuArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NN > 55 ? 2 : 3))) k_lu(LuArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   using C = Cell<NN, G>;
   constexpr int CPW = 64 / G;
   const int wave = threadIdx.x / 64;
-  const int grp = (threadIdx.x % 64) / G;
-  double* P = reinterpret_cast<double*>(smem) + (wave * CPW + grp) * (G == 64 ? lu_rows_doubles(NN) : lu_row_doubles(NN));
-  const long long m = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW + grp;
-  if (m >= a.batch) return;
+  const int lane = threadIdx.x % 64, grp = lane / G;
+  double* const S = reinterpret_cast<double*>(smem) + wave * lu_stage_doubles(NN, G);
+  const long long m0 = (static_cast<long long>(blockIdx.x) * a.wpb + wave) * CPW;
+  if (m0 >= a.batch) return;
+  const long long m = m0 + grp;
+  const bool on = m < a.batch;                 // the last wave's groups may be without a matrix
   const int n = a.n;
   const int i = Grp<G>::gl();
   double M[NN];
 #pragma unroll
-  for (int j = 0; j < NN; ++j)
-    M[j] = (i < n && j < n) ? a.A[(m * n + i) * n + j] : (i == j && i < NN ? 1.0 : 0.0);
-  int pivk[NN];
+  for (int j = 0; j < NN; ++j) M[j] = i == j ? 1.0 : 0.0;
+  // runs of rows: r0 .. r0 + nr - 1 of one matrix, or all rows of the wave's
+  const int mats = static_cast<int>(min(static_cast<long long>(CPW), a.batch - m0));
+  const int step = G == 64 ? kLuRows : NN;
+  double* const A0 = a.A + m0 * n * n;
+  for (int r0 = 0; r0 < n; r0 += step) {
+    const int nr = min(step, n - r0);
+    const int cnt = G == 64 ? nr * n : mats * n * n;
+    wsync();
+#pragma unroll 8
+    for (int e = lane; e < cnt; e += 64) S[e] = A0[r0 * n + e];
+    wsync();
+    const int r = i - r0;
+    if (on && r >= 0 && r < nr) {
+      const double* row = S + (G == 64 ? r * n : (grp * n + i) * n);
+      if (n == NN) {
+#pragma unroll
+        for (int j = 0; j < NN; ++j) M[j] = row[j];
+      } else {
+        // entries past the row's end are read (within S) and not used
+#pragma unroll
+        for (int j = 0; j < NN; ++j) {
+          const double v = row[j];
+          M[j] = j < n ? v : 0.0;
+        }
+      }
+    }
+  }
+  wsync();
+  int piv = 0;
   int pos;
   double rdiag;
-  const int info = C::lu(M, pos, rdiag, P, pivk);
-  if (i < n) {
+  const int info = C::lu(M, pos, rdiag, S + (G == 64 ? 0 : grp * lu_row_doubles(NN)), &piv);
+  for (int r0 = 0; r0 < n; r0 += step) {
+    const int nr = min(step, n - r0);
+    const int cnt = G == 64 ? nr * n : mats * n * n;
+    const int r = i - r0;
+    wsync();
+    if (on && r >= 0 && r < nr) {
+      double* row = S + (G == 64 ? r * n : (grp * n + i) * n);
 #pragma unroll
-    for (int j = 0; j < NN; ++j)
-      if (j < n) a.A[(m * n + i) * n + j] = M[j];
+      for (int j = 0; j < NN; ++j)
+        if (j < n) row[j] = M[j];
+    }
+    wsync();
+#pragma unroll 8
+    for (int e = lane; e < cnt; e += 64) A0[r0 * n + e] = S[e];
   }
-  if (i == 0) {
-#pragma unroll
-    for (int k = 0; k < NN; ++k)
-      if (k < n) a.piv[m * n + k] = pivk[k];
-    a.info[m] = info;
-  }
+  if (!on) return;
+  if (i < n) a.piv[m * n + i] = piv;
+  if (i == 0) a.info[m] = info;
   if (a.b) {
     const double b = i < n ? a.b[m * n + i] : 0.0;
     const double x = C::solve(M, pos, rdiag, b);
@@ -1737,7 +1806,9 @@ hipError_t launch_lu(const Variant& v, int grid, const LuArgs& a, hipStream_t st
   if (!fn) return hipErrorInvalidValue;
   LuArgs copy = a;
   void* args[] = {&copy};
-  const size_t lds = sizeof(double) * (v.g == 64 ? lu_rows_doubles(v.nn) : lu_row_doubles(v.nn)) * a.wpb * (64 / v.g);
+  const size_t lds = sizeof(double) * lu_stage_doubles(v.nn, v.g) * a.wpb;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+  if (e != hipSuccess) return e;
   return hipLaunchKernel(fn, dim3(grid), dim3(64 * a.wpb), args, lds, st);
 }
 

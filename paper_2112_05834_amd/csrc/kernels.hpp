@@ -72,6 +72,7 @@ struct EvalArgs {
   double* f;
   double* J;
   int cell_doubles;
+  int share_j;
   int wpb;
   double* ws;
   long long ws_stride;
