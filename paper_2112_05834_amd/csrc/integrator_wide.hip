@@ -11,16 +11,19 @@
 //
 // The LU is a left-looking blocked getrf that never moves a row in HBM:
 // the row interchanges are kept as a permutation, so physical row q of M
-// stays at offset q of every column. Panel by panel (12 columns), the panel
-// is first brought up to date with every finished column to its left, each
-// wave holding three of its columns in registers while the finished columns
-// stream through LDS twelve at a time; the four waves then factor the panel
-// with one row per lane and write it back. Every element sees the same
+// stays at offset q of every column. Panel by panel, the panel is first
+// brought up to date with every finished column to its left, each wave
+// holding a few of its columns in registers; the four waves then factor the
+// panel with one row per lane and write it back. Every element sees the same
 // sequence of operations as in an unblocked row-swapping LU, in the same
-// order, so the factors do not depend on the blocking.
+// order, so the factors do not depend on the blocking. There are two: lu_m, the
+// integration's (the multipliers go from HBM to registers), and lu_w, the batched
+// entry point's, which also takes matrices that are not finite as an unblocked
+// LU does (the multipliers go through LDS).
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -37,6 +40,9 @@ constexpr int kNB = kWidePanel;
 // rather than 12 spreads the transposed stores of consecutive row pairs over
 // more LDS banks, and keeps every row 16-byte aligned.
 constexpr int kLS = 14;
+// The integration's LU: panel width, row stride of the panel in LDS, columns of a
+// block, row stride of a wave's table.
+constexpr int kMB = 16, kMS = 18, kBK = 8, kTW = 14;
 
 // Per-cell LDS area. Region A (right-hand-side buffers) and region B (the
 // LU's two 12-column buffers) are never live at the same time and share
@@ -45,7 +51,7 @@ constexpr int kLS = 14;
 struct Wide {
   double *C, *gRT, *hRT, *RB;                   // A: ns, ns, ns, 5 nr
   double *buf0, *buf1;                          // B: the LU's two 12-column buffers, kLS ld each
-  double *y, *f0, *fs, *ys, *yn, *v, *u[4];     // 8 distinct vectors of ld
+  double *y, *f0, *fs, *ys, *yn, *v, *u;        // 8 distinct vectors of ld (u: 4)
   double* red;                                  // 16
   double* ub;                                   // 144: per wave, 12 x 3 values of the LU's U block
   int* piv;                                     // ld: getrf's interchange at each step
@@ -58,8 +64,10 @@ struct Wide {
 
 __host__ __device__ inline int wide_region(int ns, int nr, int ld) {
   const int a = 3 * ns + 5 * nr;
-  const int b = 2 * kLS * ld;
-  return ((a > b ? a : b) + 1) & ~1;
+  const int b = 2 * kLS * ld;                   // lu_w: two buffers
+  const int m = kMS * ld + 4 * kBK * kTW;       // lu_m: the panel and the waves' tables
+  const int bm = b > m ? b : m;
+  return ((a > bm ? a : bm) + 1) & ~1;
 }
 
 // doubles: region, 8 vectors, reduction scratch, U block; ints: piv, perm,
@@ -83,7 +91,7 @@ __device__ inline Wide wide_area(double* base, int ns, int nr, int ld) {
   W.yn = W.fs;
   W.v = q + 3 * ld;
   W.ys = W.v;
-  for (int k = 0; k < 4; ++k) W.u[k] = q + (4 + k) * ld;
+  W.u = q + 4 * ld;
   W.red = q + 8 * ld;
   W.ub = W.red + 16;
   int* ip = reinterpret_cast<int*>(W.ub + 144);
@@ -107,6 +115,60 @@ __device__ __forceinline__ double bsum(double v, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// The per-cell area is LDS; pointers into it are generic in the Wide struct.
+// Converted to the LDS address space, accesses compile to LDS instructions
+// (not flat ones, whose completion is counted together with global loads)
+// even where the compiler cannot trace them to the shared array.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds(T* p) {
+  return (__attribute__((address_space(3))) T*)p;
+}
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(3))) T* lds(const T* p) {
+  return (const __attribute__((address_space(3))) T*)p;
+}
+// a pair of doubles as a native vector (128-bit LDS and global accesses)
+typedef double dv2 __attribute__((ext_vector_type(2)));
+// the same for the workspace slot in HBM (global loads and stores)
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* glb(T* p) {
+  return (__attribute__((address_space(1))) T*)p;
+}
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(1))) T* glb(const T* p) {
+  return (const __attribute__((address_space(1))) T*)p;
+}
+
+// ---- wave-wide primitives (all 64 lanes active) ---------------------------------
+// a wave-uniform value in a scalar register
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// The double at a uniform address plus a lane's offset in bytes: one load with a
+// scalar base and a 32-bit offset register, where the offset passes through
+// here() in the block of the loads (extended elsewhere, every load would take a
+// 64-bit vector add of its own).
+__device__ __forceinline__ unsigned here(unsigned off) {
+  asm volatile("" : "+v"(off));
+  return off;
+}
+__device__ __forceinline__ double ld_off(const double* base, unsigned off) {
+  const auto* b = reinterpret_cast<const __attribute__((address_space(1))) char*>(glb(base));
+  return *reinterpret_cast<const __attribute__((address_space(1))) double*>(b + off);
+}
+__device__ __forceinline__ void st_off(double* base, unsigned off, double v) {
+  auto* b = reinterpret_cast<__attribute__((address_space(1))) char*>(glb(base));
+  *reinterpret_cast<__attribute__((address_space(1))) double*>(b + off) = v;
+}
+
+// The thread's index, opaque: what is computed from it stays in the phase that
+// uses it. The compiler otherwise moves the addresses of every phase out of the
+// step loop and spills them, and each reload from scratch waits for every load
+// in flight.
+__device__ __forceinline__ int thread_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Loads of J for the chain rule, in batches of kJB: species rows of column t
 // (row t of the species block) or of row t (column t); indices past the last
 // species read the last one (such values are never used), so that every
@@ -115,13 +177,15 @@ __device__ __forceinline__ double bsum(double v, double* red) {
 constexpr int kJB = 16;
 __device__ __forceinline__ void jrow_load(const double* J, int ns, int ld, int t, int k0, double (&v)[kJB]) {
   asm volatile("" : "+s"(k0));
+  const unsigned off = here(8u * t);
 #pragma unroll
-  for (int q = 0; q < kJB; ++q) v[q] = J[(1 + min(k0 + q, ns - 1)) * ld + t];
+  for (int q = 0; q < kJB; ++q) v[q] = ld_off(J + (1 + min(k0 + q, ns - 1)) * ld, off);
 }
 __device__ __forceinline__ void jcol_load(const double* J, int ns, int ld, int t, int q0, double (&v)[kJB]) {
   asm volatile("" : "+s"(q0));
+  const unsigned off = here(8u * (t * ld + 1));
 #pragma unroll
-  for (int q = 0; q < kJB; ++q) v[q] = J[t * ld + 1 + min(q0 + q, ns - 1)];
+  for (int q = 0; q < kJB; ++q) v[q] = ld_off(J + min(q0 + q, ns - 1), off);
 }
 
 // ---- right-hand side and analytical Jacobian ----------------------------------
@@ -132,7 +196,7 @@ template <bool JAC>
 __device__ __forceinline__ void rhs_w(const MechArgs& A, const MechLds& L, const Wide& W, double p, const double* yv, double* fout,
                       double* J, int ld) {
   const int ns = A.ns, nr = A.nr, n = ns + 1;
-  const int t = threadIdx.x;
+  const int t = thread_here();
   const bool sp = t >= 1 && t <= ns;
   const int s = sp ? t - 1 : 0;
   const double T = yv[0];
@@ -302,31 +366,6 @@ __device__ __forceinline__ void rhs_w(const MechArgs& A, const MechLds& L, const
   __syncthreads();
 }
 
-// The per-cell area is LDS; pointers into it are generic in the Wide struct.
-// Converted to the LDS address space, accesses compile to LDS instructions
-// (not flat ones, whose completion is counted together with global loads)
-// even where the compiler cannot trace them to the shared array.
-template <class T>
-__device__ __forceinline__ __attribute__((address_space(3))) T* lds(T* p) {
-  return (__attribute__((address_space(3))) T*)p;
-}
-template <class T>
-__device__ __forceinline__ const __attribute__((address_space(3))) T* lds(const T* p) {
-  return (const __attribute__((address_space(3))) T*)p;
-}
-// a pair of doubles as a native vector (128-bit LDS and global accesses)
-typedef double dv2 __attribute__((ext_vector_type(2)));
-// the same for the workspace slot in HBM (global loads and stores)
-template <class T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* glb(T* p) {
-  return (__attribute__((address_space(1))) T*)p;
-}
-template <class T>
-__device__ __forceinline__ const __attribute__((address_space(1))) T* glb(const T* p) {
-  return (const __attribute__((address_space(1))) T*)p;
-}
-
-// ---- wave-wide primitives (all 64 lanes active) ---------------------------------
 __device__ __forceinline__ double rl_d(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
@@ -448,13 +487,9 @@ __device__ __forceinline__ void each_slot(double (&r0)[C], double (&r1)[C], doub
 }
 
 // this wave's panel columns (k0 + 3w + cc) of the matrix, rows beyond n and
-// columns beyond the panel as zero. With FORM the source is J and the
-// matrix is g I - J, formed here: each column of M is read in its original
-// form only once, by this load.
-template <bool FORM>
+// columns beyond the panel as zero
 __device__ __forceinline__ void load_cols(double (&a0)[kCW], double (&a1)[kCW], double (&a2)[kCW],
-                                          double (&a3)[kCW], const double* Sg, double g, int n, int ld, int k0,
-                                          int nb) {
+                                          double (&a3)[kCW], const double* Sg, int n, int ld, int k0, int nb) {
   asm volatile("" : "+s"(k0));    // addresses formed here, not hoisted and spilled
   const auto* S = glb(Sg);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -463,8 +498,7 @@ __device__ __forceinline__ void load_cols(double (&a0)[kCW], double (&a1)[kCW], 
 #pragma unroll
     for (int cc = 0; cc < kCW; ++cc) {
       const int c = kCW * w + cc;
-      const double v = (q < n && c < nb) ? S[(k0 + c) * ld + q] : 0.0;
-      row[cc] = FORM ? ((q == k0 + c ? g : 0.0) - v) : v;
+      row[cc] = (q < n && c < nb) ? S[(k0 + c) * ld + q] : 0.0;
     }
   });
 }
@@ -701,10 +735,7 @@ __device__ __forceinline__ void factor_panel(double* Mg, const double* Hg, int n
   if (t == 0) lds(W.ired)[15] = info;
 }
 
-// With FORM, the matrix is gm I - J (J: n x n, the same layout) and is formed
-// from J as its columns are first read; M then receives only the factors.
-template <bool FORM>
-__device__ __forceinline__ int lu_w(double* M, const double* J, double gm, int n, int ld, const Wide& W) {
+__device__ __forceinline__ int lu_w(double* M, int n, int ld, const Wide& W) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int np = (n + kNB - 1) / kNB;
   const int cnt2 = kNB * ld / 2;
@@ -719,7 +750,7 @@ __device__ __forceinline__ int lu_w(double* M, const double* J, double gm, int n
   if (t < 32) zpm[t] = 0;
   if (t == 0) ired[15] = 0;
   double A0[kCW], A1[kCW], A2[kCW], A3[kCW];
-  load_cols<FORM>(A0, A1, A2, A3, FORM ? J : M, gm, n, ld, 0, min(kNB, n));
+  load_cols(A0, A1, A2, A3, M, n, ld, 0, min(kNB, n));
   dv2 R[kPre];
   int g = 0;   // finished blocks applied so far: block g is in buffer g & 1
   __syncthreads();
@@ -772,24 +803,381 @@ __device__ __forceinline__ int lu_w(double* M, const double* J, double gm, int n
         if (q < n) HL[q * kLS + kCW * w + cc] = row[cc];
     });
     __syncthreads();
-    if (p + 1 < np) load_cols<FORM>(A0, A1, A2, A3, FORM ? J : M, gm, n, ld, k0 + kNB, min(kNB, n - k0 - kNB));
+    if (p + 1 < np) load_cols(A0, A1, A2, A3, M, n, ld, k0 + kNB, min(kNB, n - k0 - kNB));
     factor_panel(M, H, n, ld, k0, nb, W);
     __syncthreads();
   }
   return ired[15];
 }
 
-// x = M^-1 b with the factors of lu_w. b (LDS) is overwritten: the
-// substitutions run in place in physical row order; x (LDS, distinct from b)
-// receives the solution. Forward substitution in blocks of kSB columns (each
-// element receives its terms in ascending column order), then backward in
-// blocks from the bottom. Every thread loads its own physical row's entries
-// in the block's columns, two blocks ahead (three register sets, loads
-// issued unconditionally so that each wait is for one set only). The rows
-// inside the block hand theirs to wave 0 through LDS; wave 0 solves the
-// block's triangle on lanes 0..15, the solved value of each step broadcast
-// along them by DPP (row_newbcast; the backward steps multiply by the
-// diagonal's reciprocal); every thread then updates its row.
+// ---- the integration's LU -------------------------------------------------------------
+// The same left-looking LU with rows kept in place (pivoting as a permutation,
+// the factors in M, every term a product and a difference, each rounded, in
+// ascending k: the same bits as lu_w), with nothing between the waves inside a
+// panel's block applications. Panels of 16 columns; wave w holds columns 4 w ..
+// 4 w + 3 of the panel, lane l rows l + 64 s, and takes the multipliers of all
+// rows straight from M, blocks of kBK columns, two blocks ahead in registers
+// (one ahead in the largest size, which has no more registers).
+//
+// What bounds a cell is the latency of its chain of columns: one workgroup alone
+// on a CU takes about as long as two. In lu_w's scheme that chain was an LDS
+// staging and a barrier per block, and a panel step of 2200 cycles; per attempt at
+// n = 161, two workgroups a CU, the LU took 1000 thousand cycles and takes 600,
+// the solves 450 and 250; 1024 such cells 316 ms and 257, 1500 cells at n = 101
+// 185 ms and 148. Matrix instructions for the blocks were faster still (210 and
+// 130 ms) but fuse each product with its sum: one cell in some thousands then
+// takes another sequence of steps.
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
+// t = (lane J of z, by 16-lane rows) * m, rounded (added to zero by the one
+// instruction that takes the broadcast along)
+template <int J>
+__device__ __forceinline__ double bcast_mul(double z, double m) {
+  double t = 0.0;
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "+v"(t)
+      : "v"(z), "v"(m), "n"(J));
+  return t;
+}
+
+// x[j] = x[j] - (lane j of z) * m for j = J0 .. 15
+template <int J0>
+__device__ __forceinline__ void row_sub(double (&x)[kMB], double z, double m) {
+#define CHEM_F(X, J) "v_fmac_f64_dpp " X ", %[z], %[m] row_newbcast:" J " row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (kMB - J0 >= 4) {
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    asm("s_nop 1\n\t" CHEM_F("%0", "%[a]") CHEM_F("%1", "%[b]") CHEM_F("%2", "%[c]") CHEM_F("%3", "%[d]")
+        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3])
+        : [z] "v"(z), [m] "v"(m), [a] "n"(J0), [b] "n"(J0 + 1), [c] "n"(J0 + 2), [d] "n"(J0 + 3));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[J0 + i] = x[J0 + i] - t[i];
+    row_sub<J0 + 4>(x, z, m);
+  } else if constexpr (J0 < kMB) {
+    x[J0] = x[J0] - bcast_mul<J0>(z, m);
+    row_sub<J0 + 1>(x, z, m);
+  }
+#undef CHEM_F
+}
+
+// Multipliers of columns kb .. kb + kBK - 1, row l + 64 s. Every load is
+// issued (rows past ld read the last one): with loads in branches the
+// compiler's waits at the merges cover the next blocks' loads too.
+template <int NT>
+__device__ __forceinline__ void mult_load(const double* M, int ld, int kb, double (&q)[NT][kBK], int lane) {
+  asm volatile("" : "+s"(kb));      // addresses formed here, not hoisted and spilled
+  const unsigned off = here(8u * lane), offl = here(8u * min(64 * (NT - 1) + lane, ld - 1));
+  const double* p = M + kb * ld;
+#pragma unroll
+  for (int j = 0; j < kBK; ++j, p += ld) {
+#pragma unroll
+    for (int s = 0; s < NT - 1; ++s) q[s][j] = ld_off(p + 64 * s, off);
+    q[NT - 1][j] = ld_off(p, offl);
+  }
+}
+
+// this wave's columns k0 + 4 w + j of J, and of g I - J from them (zero beyond n)
+template <int NT>
+__device__ __forceinline__ void cols_load(double (&C)[NT][4], const double* J, int n, int ld, int k0, int t) {
+  asm volatile("" : "+s"(k0));
+  const int lane = t & 63, w = uni(t >> 6);
+  const unsigned off = here(8u * lane), offl = here(8u * min(64 * (NT - 1) + lane, ld - 1));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const double* p = J + min(k0 + 4 * w + j, n - 1) * ld;
+#pragma unroll
+    for (int s = 0; s < NT - 1; ++s) C[s][j] = ld_off(p + 64 * s, off);
+    C[NT - 1][j] = ld_off(p, offl);
+  }
+}
+template <int NT>
+__device__ __forceinline__ void cols_form(double (&C)[NT][4], double g, int n, int k0, int t) {
+  const int lane = t & 63, w = uni(t >> 6);
+#pragma unroll
+  for (int s = 0; s < NT; ++s) {
+    const int q = lane + 64 * s;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = k0 + 4 * w + j;
+      const double v = (q == col ? g : 0.0) - C[s][j];
+      C[s][j] = q < n && col < n ? v : 0.0;
+    }
+  }
+}
+
+// Block of columns kb .. kb + kBK - 1 (multipliers q) applied to this wave's
+// columns C. T: this wave's table, kBK rows of kTW: the block's own rows of C,
+// then their multipliers. The solved rows U come from the block's triangle;
+// then every row takes the terms of the columns before its own position: all
+// of them below the block, inside it those that the triangle gave it (the same
+// value again), none above. A masked multiplier is zero, which changes nothing
+// for finite U (where U is not finite no step is accepted).
+template <int NT>
+__device__ __forceinline__ void block_apply(double (&C)[NT][4], const int (&ps)[NT], double (&q)[NT][kBK],
+                                            __attribute__((address_space(3))) double* T, int kb, int lane) {
+  using LD2 = __attribute__((address_space(3))) dv2;
+  const int m = lane & 15, h = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < NT; ++s) {
+    const int r = ps[s] - kb;
+    if (r >= 0 && r < kBK) {
+      LD2* d = reinterpret_cast<LD2*>(T + r * kTW);
+      d[0] = dv2{C[s][0], C[s][1]};
+      d[1] = dv2{C[s][2], C[s][3]};
+#pragma unroll
+      for (int j = 0; j < kBK / 2; ++j) d[2 + j] = dv2{q[s][2 * j], q[s][2 * j + 1]};
+    }
+  }
+  wsync();
+  // lane 16 h + m holds row m of column h; the multipliers are masked, which
+  // keeps the selects off the chain
+  double x, lr[kBK];
+  {
+    const auto* d = T + (m & (kBK - 1)) * kTW;
+    x = d[h];
+#pragma unroll
+    for (int j = 0; j < kBK / 2; ++j) {
+      const dv2 v = reinterpret_cast<const LD2*>(d + 4)[j];
+      lr[2 * j] = v.x;
+      lr[2 * j + 1] = v.y;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NT; ++s)
+#pragma unroll
+    for (int j = 0; j < kBK; ++j) q[s][j] = ps[s] - kb > j ? q[s][j] : 0.0;
+  static_for<kBK - 1>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    x = x - bcast_mul<j>(x, m > j ? lr[j] : 0.0);
+  });
+  wsync();
+#pragma unroll
+  for (int j = 0; j < kBK; ++j) {
+    double U[4];                 // uniform
+#pragma unroll
+    for (int c = 0; c < 4; ++c) U[c] = rl_d(x, 16 * c + j);
+#pragma unroll
+    for (int s = 0; s < NT; ++s) {
+      double t[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) t[c] = q[s][j] * U[c];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) C[s][c] = C[s][c] - t[c];
+    }
+  }
+}
+
+// the maximum over the wave's lanes
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+#define CHEM_M(CTRL) v = max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true)))
+  CHEM_M(0xB1);     // quad_perm 1 0 3 2
+  CHEM_M(0x4E);     // quad_perm 2 3 0 1
+  CHEM_M(0x141);    // row_half_mirror
+  CHEM_M(0x140);    // row_mirror
+  CHEM_M(0x142);    // row_bcast 15
+  CHEM_M(0x143);    // row_bcast 31
+#undef CHEM_M
+  return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+
+// the value of 16-lane row r (uniform) in all four rows
+__device__ __forceinline__ double from_row(double v, int r) {
+  const auto l2 = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto h2 = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  const unsigned lo = r & 2 ? l2[1] : l2[0], hi = r & 2 ? h2[1] : h2[0];
+  const auto l1 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h1 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __hiloint2double(r & 1 ? h1[1] : h1[0], r & 1 ? l1[1] : l1[0]);
+}
+
+// All four waves: factor panel columns k0 .. k0 + nb - 1, the panel in LDS as
+// rows of kMB doubles (H[q * kMS + c], physical row q), with factor_panel's
+// choice of pivots; pq: the logical position of row q = threadIdx.x, updated. A
+// column is one chain from the keys to the updated rows, so the steps on it are
+// kept short: the key is the upper word of |a| (one above it, 0 for a row that
+// cannot be the pivot), its maximum six fused DPP steps, and only rows that tie
+// in it compare lower words and positions; after the column's barrier one
+// read brings the four candidates' keys (lane % 4: candidate; compared in two
+// DPP steps) and one their rows (16-lane row r: candidate r, lane j: entry j);
+// the winner's row goes to every 16-lane row by swaps, and the updates
+// broadcast its entries by DPP inside the multiplication.
+// Returns info of the columns up to here.
+__device__ __forceinline__ int factor_m(double* M, const double* Hg, int n, int ld, int k0, int nb, int t, int& pos,
+                                        int info, double* candg) {
+  constexpr int kCand = 2 + kMB;   // per wave and parity: key, code, row entries
+  using LD2 = __attribute__((address_space(3))) dv2;
+  using LI4 = __attribute__((address_space(3))) i4;
+  auto* H = lds(Hg);
+  auto* cand = lds(candg);
+  const int w = t >> 6, lane = t & 63;
+  const int q = t;
+  int pq = pos;
+  double P[kMB];
+  {
+    const LD2* r = reinterpret_cast<const LD2*>(H + (q < n ? q : 0) * kMS);
+#pragma unroll
+    for (int j = 0; j < kMB / 2; ++j) {
+      const dv2 v = r[j];
+      P[2 * j] = v.x;
+      P[2 * j + 1] = v.y;
+    }
+  }
+  static_for<kMB>([&](auto cc) {
+    constexpr int c = decltype(cc)::value;
+    if (c >= nb) return;
+    const int k = k0 + c;
+    const unsigned hi = static_cast<unsigned>(__double2hiint(P[c])) & 0x7fffffffu;
+    const unsigned lo = static_cast<unsigned>(__double2loint(P[c]));
+    unsigned key = hi + 1u, other = pq == k ? 0xffffffffu : 0u;
+    asm volatile("" : "+v"(key), "+v"(other));     // selects, not branches
+    key = P[c] != P[c] ? other : key;
+    key = pq < k ? 0u : key;
+    const int code = pq * 256 + q;
+    const unsigned mk = wave_max_u32(key);
+    unsigned long long bal = __ballot(key == mk);
+    if (mk != 0 && __popcll(bal) != 1) {
+      const unsigned ml = wave_max_u32(key == mk ? lo : 0u);
+      bal = __ballot(key == mk && lo == ml);
+      if (__popcll(bal) != 1) {
+        const unsigned mc = wave_max_u32(key == mk && lo == ml ? ~static_cast<unsigned>(code) : 0u);
+        bal = __ballot(key == mk && ~static_cast<unsigned>(code) == mc);
+      }
+    }
+    auto* set = cand + (c & 1) * 4 * kCand;
+    if (lane == __ffsll(static_cast<long long>(bal)) - 1) {
+      auto* slot = set + w * kCand;
+      *reinterpret_cast<LI4*>(slot) = i4{static_cast<int>(lo), static_cast<int>(mk), code, 0};
+      LD2* r2 = reinterpret_cast<LD2*>(slot + 2);
+#pragma unroll
+      for (int j = c / 2; j < kMB / 2; ++j) r2[j] = dv2{P[2 * j], P[2 * j + 1]};
+    }
+    __syncthreads();
+    const i4 kc = *reinterpret_cast<const LI4*>(set + (lane & 3) * kCand);
+    double z = set[(lane >> 4) * kCand + 2 + (lane & 15)];
+    unsigned bl = static_cast<unsigned>(kc.x), bh = static_cast<unsigned>(kc.y);
+    int bc = kc.z;
+    // the largest key, then the smallest code
+#define CHEM_W(CTRL) { \
+      const unsigned l2 = static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(bl), CTRL, 0xf, 0xf, true)); \
+      const unsigned h2 = static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(bh), CTRL, 0xf, 0xf, true)); \
+      const int c2 = __builtin_amdgcn_mov_dpp(bc, CTRL, 0xf, 0xf, true); \
+      const unsigned long long a2 = static_cast<unsigned long long>(h2) << 32 | l2; \
+      const unsigned long long a1 = static_cast<unsigned long long>(bh) << 32 | bl; \
+      const bool better = a2 > a1 || (a2 == a1 && c2 < bc); \
+      bl = better ? l2 : bl; \
+      bh = better ? h2 : bh; \
+      bc = better ? c2 : bc; }
+    CHEM_W(0xB1)
+    CHEM_W(0x4E)
+#undef CHEM_W
+    bc = __builtin_amdgcn_readfirstlane(bc);
+    const int pv = bc >> 8, qs = bc & 255;
+    z = from_row(z, qs >> 6);
+    const double akk = rl_d(z, c);
+    if (q == qs) {
+      pq = k;
+    } else if (pq == k) {
+      pq = pv;
+    }
+    if (akk == 0.0 && !info) info = k + 1;
+    // rows below the pivot; a multiplier of zero leaves the others (their
+    // later entries of this panel would change only where the pivot row is
+    // not finite, and no such step is accepted)
+    double l = P[c] / akk;
+    asm volatile("" : "+v"(l));
+    const bool below = pq > k && akk != 0.0;
+    P[c] = below ? l : P[c];
+    row_sub<c + 1>(P, z, below ? l : 0.0);
+    if (q < n) st_off(M + k * ld, here(8u * q), P[c]);
+  });
+  pos = pq;
+  return info;
+}
+
+// Factors of g I - J (J: n x n, column-major, ld) into M. Returns the first
+// zero pivot column + 1, 0 if none.
+template <int NT>
+__device__ __forceinline__ int lu_m(double* M, const double* J, double g, int n, int ld, const Wide& W) {
+  using LD2 = __attribute__((address_space(3))) dv2;
+  const int t = thread_here(), lane = t & 63, w = t >> 6;
+  const int np = (n + kMB - 1) / kMB;
+  auto* pos = lds(W.pos);
+  double* const H = W.buf0;
+  auto* HL = lds(H);
+  auto* T = HL + kMS * ld + w * (kBK * kTW);
+  int pq = t < n ? t : -1, info = 0;
+  constexpr bool kAhead = NT < 4;      // registers
+  double C[NT][4], u[NT][kBK], v[NT][kBK], x[NT][kBK];
+  cols_load(C, J, n, ld, 0, t);
+  for (int p = 0; p < np; ++p) {
+    const int k0 = p * kMB, nb = min(kMB, n - k0), nblk = k0 / kBK;
+    cols_form(C, g, n, k0, t);
+    if (p > 0) {
+      int ps[NT];
+#pragma unroll
+      for (int s = 0; s < NT; ++s) {
+        const int q = lane + 64 * s;
+        ps[s] = q < ld ? pos[q] : -1;
+      }
+      auto L = [&](int b) { return min(b, nblk - 1) * kBK; };
+      if (p == 1 || !kAhead) mult_load(M, ld, 0, u, lane);
+      if constexpr (NT < 4) {
+        mult_load(M, ld, kBK, v, lane);
+        for (int b = 0; b < nblk; b += 3) {
+          mult_load(M, ld, L(b + 2), x, lane);
+          block_apply(C, ps, u, T, b * kBK, lane);
+          mult_load(M, ld, L(b + 3), u, lane);
+          if (b + 1 < nblk) block_apply(C, ps, v, T, (b + 1) * kBK, lane);
+          mult_load(M, ld, L(b + 4), v, lane);
+          if (b + 2 < nblk) block_apply(C, ps, x, T, (b + 2) * kBK, lane);
+        }
+      } else {
+        for (int b = 0; b < nblk; b += 2) {
+          mult_load(M, ld, L(b + 1), v, lane);
+          block_apply(C, ps, u, T, b * kBK, lane);
+          mult_load(M, ld, L(b + 2), u, lane);
+          block_apply(C, ps, v, T, (b + 1) * kBK, lane);
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < NT; ++s) {
+      const int q = lane + 64 * s;
+      if (q < n) {
+        LD2* d = reinterpret_cast<LD2*>(HL + q * kMS + 4 * w);
+        d[0] = dv2{C[s][0], C[s][1]};
+        d[1] = dv2{C[s][2], C[s][3]};
+      }
+    }
+    __syncthreads();
+    // the next panel's columns and first block arrive while this one is factored
+    // (panel 1's block is not there yet)
+    if (p + 1 < np) cols_load(C, J, n, ld, k0 + kMB, t);
+    if (kAhead && p > 0) mult_load(M, ld, 0, u, lane);
+    info = factor_m(M, H, n, ld, k0, nb, t, pq, info, W.ub);
+    if (t < ld) pos[t] = pq;
+    __syncthreads();
+  }
+  return info;
+}
+
+// x = M^-1 b with the factors of lu_w or lu_m; b and x in LDS, distinct.
+// Thread t keeps the element of its own physical row in a register. Forward
+// substitution in blocks of kSB columns (each element receives its terms in
+// ascending column order), then backward in blocks from the bottom. Every
+// thread loads its own row's entries in the block's columns, two blocks ahead
+// (three register sets, loads issued unconditionally so that each wait is for
+// one set only). The rows inside the block hand theirs and their element to
+// wave 0 through LDS; wave 0 solves the block's triangle by 16-lane rows (all
+// four alike), the solved value of each step broadcast by DPP inside the fused
+// multiply-add; every thread then updates its own element.
 constexpr int kSB = 16;
 
 // row t's entries in columns k0 .. k0 + kSB - 1 when the row takes part in
@@ -798,117 +1186,129 @@ constexpr int kSB = 16;
 // one register set) while the rows left out cost no memory traffic of their
 // own; such values are never used. k0 passes through an empty asm so that
 // the addresses are formed here, not hoisted out of the loops and spilled.
-__device__ __forceinline__ void solve_load(const double* Mg, int n, int ld, int k0, bool need, double (&v)[kSB]) {
+__device__ __forceinline__ void solve_load(const double* M, int n, int ld, int k0, int t, bool need, double (&v)[kSB]) {
   asm volatile("" : "+s"(k0));
-  const auto* M = glb(Mg) + (need ? threadIdx.x : 0);
+  const unsigned off = here(need ? 8u * t : 0u);
+  const double* p = M + k0 * ld;
 #pragma unroll
-  for (int j = 0; j < kSB; ++j) v[j] = M[min(k0 + j, n - 1) * ld];
+  for (int j = 0; j < kSB; ++j) {
+    v[j] = ld_off(p, off);
+    p += k0 + j + 1 < n ? ld : 0;
+  }
 }
 
-template <bool FWD>
-__device__ __forceinline__ void solve_block(int k0, int n, int pt, const double (&v)[kSB], const Wide& W,
-                                            __attribute__((address_space(3))) double* b) {
-  using LD = __attribute__((address_space(3))) double;
+constexpr int kXS = kSB + 2;            // row stride of the block's rows in LDS: entries, element
+
+// columns k0 .. k0 + nb - 1; PART: rows outside the block may take fewer than kSB
+// terms (the backward substitution's last block)
+template <bool FWD, bool PART>
+__device__ __forceinline__ void solve_block(int k0, int nb, int t, int pt, const double (&v)[kSB], const Wide& W, double& a) {
   using LD2 = __attribute__((address_space(3))) dv2;
-  const int t = threadIdx.x;
-  const int nb = min(kSB, n - k0);
-  LD* T = lds(W.buf1);                  // the block rows' entries, kSB x kSB
-  LD* xb = lds(W.ub);                  // the block's solved values
+  auto* T = lds(W.buf1);               // the block rows' entries and elements, kSB x kXS
+  auto* xb = lds(W.ub);                // the block's solved values
   const int rel = pt - k0;
-  if (rel >= 0 && rel < nb) {
-    LD2* d = reinterpret_cast<LD2*>(T + rel * kSB);
+  const bool in = rel >= 0 && rel < kSB;
+  if (in) {
+    LD2* d = reinterpret_cast<LD2*>(T + rel * kXS);
 #pragma unroll
     for (int j = 0; j < kSB / 2; ++j) d[j] = dv2{v[2 * j], v[2 * j + 1]};
+    T[rel * kXS + kSB] = a;
   }
   __syncthreads();
   if (t < 64) {
-    const int r = t < nb ? lds(W.perm)[k0 + t] : 0;
-    double lc[kSB];
+    const int c = t & (kSB - 1), r = min(c, nb - 1);
+    // the multipliers are masked rather than the updates, which keeps the
+    // selects off the chain of dependent broadcasts (a zero multiplier
+    // leaves xv unchanged for finite z; lanes past the block hold zero)
+    double lm[kSB];
     {
-      const LD2* rr = reinterpret_cast<const LD2*>(T + (t < nb ? t : 0) * kSB);
+      const LD2* rr = reinterpret_cast<const LD2*>(T + r * kXS);
 #pragma unroll
       for (int j = 0; j < kSB / 2; ++j) {
         const dv2 x = rr[j];
-        lc[2 * j] = x.x;
-        lc[2 * j + 1] = x.y;
+        lm[2 * j] = x.x;
+        lm[2 * j + 1] = x.y;
       }
     }
-    double xv = t < nb ? b[r] : 0.0;
-    // the multipliers are masked rather than the updates, which keeps the
-    // selects off the chain of dependent broadcasts (a zero multiplier
-    // leaves xv unchanged for finite z)
+    double xv = T[r * kXS + kSB];
+    xv = c < nb ? xv : 0.0;
     if (FWD) {
-#pragma unroll
-      for (int j = 0; j + 1 < kSB; ++j) {
-        if (j + 1 < nb) {
-          const double lm = (t > j && t < nb) ? lc[j] : 0.0;
-          const double z = row_share(xv, j);
-          xv = xv - lm * z;
-        }
-      }
+      static_for<kSB - 1>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        xv = xv - bcast_mul<j>(xv, c > j ? lm[j] : 0.0);
+      });
     } else {
       // the diagonal's reciprocals, all lanes at once; lane j's value is
       // final once the steps above it are done (its multipliers from then
       // on are zero), and is scaled by its reciprocal when broadcast and at
       // the end
-      const double rdg = 1.0 / (t < nb ? T[t * kSB + t] : 1.0);
-#pragma unroll
-      for (int j = kSB - 1; j >= 0; --j) {
-        if (j < nb) {
-          const double lm = t < j ? lc[j] : 0.0;
-          const double z = row_share(xv * rdg, j);
-          xv = xv - lm * z;
-        }
-      }
+      const double rdg = 1.0 / T[r * (kXS + 1)];
+      static_for<kSB>([&](auto jc) {
+        constexpr int j = kSB - 1 - decltype(jc)::value;
+        xv = xv - bcast_mul<j>(xv * rdg, c < j && (!PART || j < nb) ? lm[j] : 0.0);
+      });
       xv = xv * rdg;
     }
-    if (t < nb) {
-      b[r] = xv;
-      xb[t] = xv;
-    }
+    if (t < kSB) xb[t] = xv;
   }
   __syncthreads();
-  if (FWD ? pt >= k0 + nb : (pt >= 0 && pt < k0)) {
-    double a = b[t];
+  if (in) {
+    a = xb[rel];
+  } else if (FWD ? rel >= 0 : rel < 0) {
+    double z[kSB];
+#pragma unroll
+    for (int j = 0; j < kSB / 2; ++j) {
+      const dv2 x = reinterpret_cast<const LD2*>(xb)[j];
+      z[2 * j] = x.x;
+      z[2 * j + 1] = x.y;
+    }
 #pragma unroll
     for (int j = 0; j < kSB; ++j)
-      if (j < nb) a = a - v[j] * xb[j];
-    b[t] = a;
+      if (!PART || j < nb) a = a - v[j] * z[j];
   }
 }
 
-__device__ __forceinline__ void solve_w(const double* M, int n, int ld, const Wide& W, double* bg, double* xg) {
-  auto* b = lds(bg);
-  auto* x = lds(xg);
-  const int t = threadIdx.x;
+__device__ __forceinline__ void solve_w(const double* M, int n, int ld, const Wide& W, const double* b, double* x) {
+  const int t = thread_here();
   const int pt = t < n ? lds(W.pos)[t] : -1;   // logical position of physical row t
+  double a = t < n ? lds(b)[t] : 0.0;
   const int nblk = (n + kSB - 1) / kSB;
-  const int last = (nblk - 1) * kSB;
+  auto load_f = [&](int i, double (&v)[kSB]) {
+    const int k = min(i, nblk - 1) * kSB;
+    solve_load(M, n, ld, k, t, pt >= k, v);
+  };
+  auto load_b = [&](int i, double (&v)[kSB]) {
+    const int k = max(i, 0) * kSB;
+    solve_load(M, n, ld, k, t, pt >= 0 && pt < k + kSB, v);
+  };
   double v0[kSB], v1[kSB], v2[kSB];
-  // forward: blocks 0, 1, 2, ...; loads past the last block repeat it
-  solve_load(M, n, ld, 0, pt >= 0, v0);
-  solve_load(M, n, ld, min(kSB, last), pt >= min(kSB, last), v1);
+  // forward: blocks 0, 1, 2, ... (below the last one no rows are left); loads past
+  // it repeat it
+  load_f(0, v0);
+  load_f(1, v1);
   for (int i = 0; i < nblk; i += 3) {
-    solve_load(M, n, ld, min((i + 2) * kSB, last), pt >= min((i + 2) * kSB, last), v2);
-    solve_block<true>(i * kSB, n, pt, v0, W, b);
-    solve_load(M, n, ld, min((i + 3) * kSB, last), pt >= min((i + 3) * kSB, last), v0);
-    if (i + 1 < nblk) solve_block<true>((i + 1) * kSB, n, pt, v1, W, b);
-    solve_load(M, n, ld, min((i + 4) * kSB, last), pt >= min((i + 4) * kSB, last), v1);
-    if (i + 2 < nblk) solve_block<true>((i + 2) * kSB, n, pt, v2, W, b);
+    load_f(i + 2, v2);
+    solve_block<true, false>(i * kSB, min(kSB, n - i * kSB), t, pt, v0, W, a);
+    load_f(i + 3, v0);
+    if (i + 1 < nblk) solve_block<true, false>((i + 1) * kSB, min(kSB, n - (i + 1) * kSB), t, pt, v1, W, a);
+    load_f(i + 4, v1);
+    if (i + 2 < nblk) solve_block<true, false>((i + 2) * kSB, min(kSB, n - (i + 2) * kSB), t, pt, v2, W, a);
   }
-  // backward: blocks nblk - 1, nblk - 2, ...; loads past the first repeat it
-  solve_load(M, n, ld, last, pt >= 0 && pt < last + kSB, v0);
-  solve_load(M, n, ld, max(last - kSB, 0), pt >= 0 && pt < max(last - kSB, 0) + kSB, v1);
-  for (int i = nblk - 1; i >= 0; i -= 3) {
-    solve_load(M, n, ld, max((i - 2) * kSB, 0), pt >= 0 && pt < max((i - 2) * kSB, 0) + kSB, v2);
-    solve_block<false>(i * kSB, n, pt, v0, W, b);
-    solve_load(M, n, ld, max((i - 3) * kSB, 0), pt >= 0 && pt < max((i - 3) * kSB, 0) + kSB, v0);
-    if (i - 1 >= 0) solve_block<false>((i - 1) * kSB, n, pt, v1, W, b);
-    solve_load(M, n, ld, max((i - 4) * kSB, 0), pt >= 0 && pt < max((i - 4) * kSB, 0) + kSB, v1);
-    if (i - 2 >= 0) solve_block<false>((i - 2) * kSB, n, pt, v2, W, b);
+  // backward: the last block, then the full ones from the bottom; loads past
+  // the first repeat it
+  load_b(nblk - 1, v2);
+  load_b(nblk - 2, v0);
+  load_b(nblk - 3, v1);
+  solve_block<false, true>((nblk - 1) * kSB, n - (nblk - 1) * kSB, t, pt, v2, W, a);
+  for (int i = nblk - 2; i >= 0; i -= 3) {
+    load_b(i - 2, v2);
+    solve_block<false, false>(i * kSB, kSB, t, pt, v0, W, a);
+    load_b(i - 3, v0);
+    if (i - 1 >= 0) solve_block<false, false>((i - 1) * kSB, kSB, t, pt, v1, W, a);
+    load_b(i - 4, v1);
+    if (i - 2 >= 0) solve_block<false, false>((i - 2) * kSB, kSB, t, pt, v2, W, a);
   }
-  __syncthreads();
-  if (t < n) x[t] = b[lds(W.perm)[t]];
+  if (pt >= 0) lds(x)[pt] = a;
   __syncthreads();
 }
 
@@ -1006,7 +1406,10 @@ __device__ __forceinline__ void integrate_w(const MechArgs& A, const MechLds& L,
     // M = g I - J, formed by the LU as it first reads each column
     const double g = 1.0 / (TB::gamma * hc);
     __syncthreads();
-    const int info = lu_w<true>(M, J, g, n, ld, W);
+    // by the matrix's groups of 64 rows
+    const int info = ld <= 128   ? lu_m<2>(M, J, g, n, ld, W)
+                     : ld <= 192 ? lu_m<3>(M, J, g, n, ld, W)
+                                 : lu_m<4>(M, J, g, n, ld, W);
     ++att;
     if (info) {
       status = 4;
@@ -1020,7 +1423,7 @@ __device__ __forceinline__ void integrate_w(const MechArgs& A, const MechLds& L,
       if (src == kFnew) {
         if (t < n) {
           double ys = W.y[t];
-          for (int j = 0; j < st; ++j) ys = ys + TB::a[st][j] * W.u[j][t];
+          for (int j = 0; j < st; ++j) ys = ys + TB::a[st][j] * W.u[j * ld + t];
           W.ys[t] = ys;
         }
         __syncthreads();
@@ -1030,19 +1433,19 @@ __device__ __forceinline__ void integrate_w(const MechArgs& A, const MechLds& L,
       }
       if (t < n) {
         double v = src == kFy ? W.f0[t] : W.fs[t];
-        for (int j = 0; j < st; ++j) v = v + (TB::c[st][j] / hc) * W.u[j][t];
+        for (int j = 0; j < st; ++j) v = v + (TB::c[st][j] / hc) * W.u[j * ld + t];
         W.v[t] = (nb && t == ns) ? 0.0 : v;   // the bath takes no step of its own
       }
       __syncthreads();
-      solve_w(M, n, ld, W, W.v, W.u[st]);
+      solve_w(M, n, ld, W, W.v, W.u + st * ld);
     }
     double yn = 0.0, q = 0.0;
     if (t < n) {
       yn = W.y[t];
       double ev = 0.0;
       for (int j = 0; j < 4; ++j) {
-        yn = yn + TB::m[j] * W.u[j][t];
-        ev = ev + TB::e[j] * W.u[j][t];
+        yn = yn + TB::m[j] * W.u[j * ld + t];
+        ev = ev + TB::e[j] * W.u[j * ld + t];
       }
       const double sc = o.atol + o.rtol * fmax(fabs(W.y[t]), fabs(yn));
       q = ev / sc;
@@ -1212,7 +1615,7 @@ __global__ void __launch_bounds__(256) k_lu_wide(LuArgs a) {
       M[j * ld + i] = a.A[m * nn + e];
     }
     __syncthreads();
-    const int info = lu_w<false>(M, nullptr, 0.0, n, ld, W);
+    const int info = lu_w(M, n, ld, W);
     for (long long e = t; e < nn; e += kT) {
       const int i = static_cast<int>(e / n), j = static_cast<int>(e - static_cast<long long>(i) * n);
       a.A[m * nn + e] = M[j * ld + W.perm[i]];
@@ -1222,8 +1625,8 @@ __global__ void __launch_bounds__(256) k_lu_wide(LuArgs a) {
     if (a.b) {
       if (t < n) W.v[t] = a.b[m * n + t];
       __syncthreads();
-      solve_w(M, n, ld, W, W.v, W.u[0]);
-      if (t < n) a.b[m * n + t] = W.u[0][t];
+      solve_w(M, n, ld, W, W.v, W.u);
+      if (t < n) a.b[m * n + t] = W.u[t];
     }
     __syncthreads();
   }
