@@ -1692,19 +1692,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NN > 5
   }
 }
 
-__global__ void k_fill_u64(unsigned long long* p, unsigned long long v) { *p = v; }
-
-__global__ void k_copy_f64(double* dst, const double* src, long long n) {
-  for (long long i = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<long long>(gridDim.x) * blockDim.x)
-    dst[i] = src[i];
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
+// The variants with one cell per wave are a compilation unit of their own
+// (integrator_wave.hip), compiled without the machine-level hoisting of loop
+// invariants: in their step loop it moves more 64-bit constants (of log and exp,
+// mostly) into registers than there are, and each is reloaded from scratch at its
+// use, one wait after the other (54 species: 88 spilled registers with it, 21
+// without; 131 cells 16.1 ms with, 15.1 without; 32768 cells 79.7 and 77.0).
+// Variants with several cells per wave have registers to spare and lose by it
+// (9 species, 1024 cells: 5.1 ms with, 5.4 without).
 #define CHEM_VARIANTS(X) \
   X(10, 16)              \
   X(10, 64)              \
@@ -1712,6 +1712,61 @@ __global__ void k_copy_f64(double* dst, const double* src, long long n) {
   X(32, 32)              \
   X(55, 64)              \
   X(64, 64)
+#define CHEM_GROUP_VARIANTS(X) \
+  X(10, 16)                    \
+  X(16, 16)                    \
+  X(32, 32)
+#define CHEM_WAVE_VARIANTS(X) \
+  X(10, 64)                   \
+  X(55, 64)                   \
+  X(64, 64)
+#ifdef CHEM_WAVE_UNIT
+#define CHEM_UNIT_VARIANTS CHEM_WAVE_VARIANTS
+#define CHEM_UNIT(name) wave_##name
+#else
+#define CHEM_UNIT_VARIANTS CHEM_GROUP_VARIANTS
+#define CHEM_UNIT(name) group_##name
+#endif
+
+template <int NN, int G, bool P>
+static void* integrate_fn(int scheme, bool gen) {
+  if (gen)
+    return scheme == dev::kRos4 ? reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRos4, true>)
+                                : reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRodas3, true>);
+  return scheme == dev::kRos4 ? reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRos4, false>)
+                              : reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRodas3, false>);
+}
+
+// this unit's kernels; null for a variant of the other one
+void* CHEM_UNIT(integrate_kernel)(const Variant& v, bool persistent, int scheme, bool gen) {
+#define V(a, b)                                                                                        \
+  if (v.nn == a && v.g == b)                                                                           \
+    return persistent ? integrate_fn<a, b, true>(scheme, gen) : integrate_fn<a, b, false>(scheme, gen);
+  CHEM_UNIT_VARIANTS(V)
+#undef V
+  return nullptr;
+}
+
+void* CHEM_UNIT(eval_kernel)(const Variant& v) {
+#define V(a, b) \
+  if (v.nn == a && v.g == b) return reinterpret_cast<void*>(&k_eval<a, b>);
+  CHEM_UNIT_VARIANTS(V)
+#undef V
+  return nullptr;
+}
+
+void* CHEM_UNIT(lu_kernel)(const Variant& v) {
+#define V(a, b) \
+  if (v.nn == a && v.g == b) return reinterpret_cast<void*>(&k_lu<a, b>);
+  CHEM_UNIT_VARIANTS(V)
+#undef V
+  return nullptr;
+}
+
+#ifndef CHEM_WAVE_UNIT
+void* wave_integrate_kernel(const Variant& v, bool persistent, int scheme, bool gen);
+void* wave_eval_kernel(const Variant& v);
+void* wave_lu_kernel(const Variant& v);
 
 int variants_for(int n, Variant* out, int max_out) {
   // exact sizes first, then the smallest padded size
@@ -1743,23 +1798,9 @@ bool share_j(const Variant& v, int nr, int ns, int mech_bytes, int wpb, size_t l
   return v.g == 64 && can_share_j(v.nn) && wpb >= 2 && 2 * block_lds(v, nr, ns, mech_bytes, wpb, true) <= lds_per_cu;
 }
 
-template <int NN, int G, bool P>
-static void* integrate_fn(int scheme, bool gen) {
-  if (gen)
-    return scheme == dev::kRos4 ? reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRos4, true>)
-                                : reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRodas3, true>);
-  return scheme == dev::kRos4 ? reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRos4, false>)
-                              : reinterpret_cast<void*>(&k_integrate<NN, G, P, dev::kRodas3, false>);
-}
-
 static void* find_integrate(const Variant& v, bool persistent, int scheme, bool gen) {
   if (scheme != dev::kRodas3 && scheme != dev::kRos4) return nullptr;
-#define V(a, b)                                                                                        \
-  if (v.nn == a && v.g == b)                                                                           \
-    return persistent ? integrate_fn<a, b, true>(scheme, gen) : integrate_fn<a, b, false>(scheme, gen);
-  CHEM_VARIANTS(V)
-#undef V
-  return nullptr;
+  return v.g == 64 ? wave_integrate_kernel(v, persistent, scheme, gen) : group_integrate_kernel(v, persistent, scheme, gen);
 }
 
 hipError_t launch_integrate(const Variant& v, bool persistent, int grid, const IntegrateArgs& a,
@@ -1784,11 +1825,7 @@ int integrate_blocks_per_cu(const Variant& v, bool persistent, int wpb, size_t l
 }
 
 hipError_t launch_eval(const Variant& v, int grid, const EvalArgs& a, size_t lds_bytes, hipStream_t st) {
-  void* fn = nullptr;
-#define V(x, y) \
-  if (v.nn == x && v.g == y) fn = reinterpret_cast<void*>(&k_eval<x, y>);
-  CHEM_VARIANTS(V)
-#undef V
+  void* fn = v.g == 64 ? wave_eval_kernel(v) : group_eval_kernel(v);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
   if (e != hipSuccess) return e;
@@ -1798,11 +1835,7 @@ hipError_t launch_eval(const Variant& v, int grid, const EvalArgs& a, size_t lds
 }
 
 hipError_t launch_lu(const Variant& v, int grid, const LuArgs& a, hipStream_t st) {
-  void* fn = nullptr;
-#define V(x, y) \
-  if (v.nn == x && v.g == y) fn = reinterpret_cast<void*>(&k_lu<x, y>);
-  CHEM_VARIANTS(V)
-#undef V
+  void* fn = v.g == 64 ? wave_lu_kernel(v) : group_lu_kernel(v);
   if (!fn) return hipErrorInvalidValue;
   LuArgs copy = a;
   void* args[] = {&copy};
@@ -1810,6 +1843,14 @@ hipError_t launch_lu(const Variant& v, int grid, const LuArgs& a, hipStream_t st
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
   return hipLaunchKernel(fn, dim3(grid), dim3(64 * a.wpb), args, lds, st);
+}
+
+static __global__ void k_fill_u64(unsigned long long* p, unsigned long long v) { *p = v; }
+
+static __global__ void k_copy_f64(double* dst, const double* src, long long n) {
+  for (long long i = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; i < n;
+       i += static_cast<long long>(gridDim.x) * blockDim.x)
+    dst[i] = src[i];
 }
 
 hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, hipStream_t st) {
@@ -1824,5 +1865,7 @@ hipError_t launch_copy_f64(double* dst, const double* src, long long n, hipStrea
   hipLaunchKernelGGL(k_copy_f64, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, dst, src, n);
   return hipGetLastError();
 }
+
+#endif  // CHEM_WAVE_UNIT
 
 }  // namespace chemk
