@@ -4,8 +4,10 @@
 // cell per wave; G = 16: four cells per wave), with G >= n = Ns + 1. Lane i
 // of the group owns state component i (0 = T, 1..Ns = Y_1..Y_Ns) and row i of
 // the Rosenbrock matrix M = I/(gamma h) - J, kept in registers. The analytical
-// Jacobian is assembled row-wise in the group's LDS area, from the mechanism
-// image that every block stages in LDS; it stays there across rejected steps.
+// Jacobian is assembled row-wise in an LDS area, from the mechanism image that
+// every block stages in LDS. The area is the group's own, and keeps J across
+// rejected steps, or (34 to 55 components) shared by two waves, which is what
+// lets two waves run on a SIMD; J is then formed again after a rejected step.
 //
 // Arithmetic per cell does not depend on G, on the cell's position in the
 // grid or on the schedule: reductions follow one fixed pairing tree over 64
