@@ -283,16 +283,28 @@ int chem_solver_create(const chem_mech* m, const chem_opts* o, int32_t dev, chem
   s->mech_fp = fnv1a(P.blob.data(), P.blob.size(), kFnvBasis);
   s->mech_fp = fnv1a(P.nasa.data(), P.nasa.size() * sizeof(double), s->mech_fp);
   s->mech_fp = fnv1a(P.W.data(), P.W.size() * sizeof(double), s->mech_fp);
-  HIP_TRY(hipMalloc(&s->d_blob, P.blob.size()), "hipMalloc");
-  HIP_TRY(hipMemcpy(s->d_blob, P.blob.data(), P.blob.size(), hipMemcpyHostToDevice), "hipMemcpy");
-  if (!P.rec.empty()) {
-    HIP_TRY(hipMalloc(&s->d_rec, P.rec.size()), "hipMalloc");
-    HIP_TRY(hipMemcpy(s->d_rec, P.rec.data(), P.rec.size(), hipMemcpyHostToDevice), "hipMemcpy");
+  // image, thermo tables and reaction records: one allocation, one copy
+  {
+    struct Part {
+      const void* p;
+      size_t n;
+    };
+    const Part part[4] = {{P.blob.data(), P.blob.size()},
+                          {P.nasa.data(), P.nasa.size() * sizeof(double)},
+                          {P.W.data(), P.W.size() * sizeof(double)},
+                          {P.rec.data(), s->wide ? 0 : P.rec.size()}};
+    size_t off[5] = {0};
+    for (int k = 0; k < 4; ++k) off[k + 1] = (off[k] + part[k].n + 255) & ~static_cast<size_t>(255);
+    std::vector<uint8_t> image(off[4]);
+    for (int k = 0; k < 4; ++k)
+      if (part[k].n) std::memcpy(image.data() + off[k], part[k].p, part[k].n);
+    HIP_TRY(hipMalloc(&s->d_blob, image.size()), "hipMalloc");
+    HIP_TRY(hipMemcpy(s->d_blob, image.data(), image.size(), hipMemcpyHostToDevice), "hipMemcpy");
+    uint8_t* d = static_cast<uint8_t*>(static_cast<void*>(s->d_blob));
+    s->d_nasa = reinterpret_cast<double*>(d + off[1]);
+    s->d_W = reinterpret_cast<double*>(d + off[2]);
+    if (part[3].n) s->d_rec = d + off[3];
   }
-  HIP_TRY(hipMalloc(&s->d_nasa, P.nasa.size() * sizeof(double)), "hipMalloc");
-  HIP_TRY(hipMemcpy(s->d_nasa, P.nasa.data(), P.nasa.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
-  HIP_TRY(hipMalloc(&s->d_W, P.W.size() * sizeof(double)), "hipMalloc");
-  HIP_TRY(hipMemcpy(s->d_W, P.W.data(), P.W.size() * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
   HIP_TRY(hipMalloc(&s->d_head, 4 * sizeof(unsigned long long)), "hipMalloc");
   HIP_TRY(hipMemset(s->d_head, 0, 4 * sizeof(unsigned long long)), "hipMemset");
   chemk::MechArgs& a = s->margs;
@@ -351,9 +363,6 @@ void chem_solver_free(chem_solver* s) {
   clear_timing(s);
   chem_model::release(s->model);
   hipFree(s->d_blob);
-  hipFree(s->d_rec);
-  hipFree(s->d_nasa);
-  hipFree(s->d_W);
   hipFree(s->d_head);
   hipFree(s->d_ping);
   hipFree(s->d_ws);
