@@ -975,11 +975,11 @@ struct Cell {
   // permute right-hand sides). With piv, lane k also receives the position
   // interchanged with k. Returns the first singular column + 1.
   // -------------------------------------------------------------------------
-  __device__ static __forceinline__ int lu(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
+  __device__ static __forceinline__ int lu(double (&M)[NN], int& pos, double& rdiag, double* P, int n, int* piv) {
     if constexpr (G == 64) {
-      return lu_wave(M, pos, rdiag, P, piv);
+      return lu_wave(M, pos, rdiag, P, n, piv);
     } else {
-      return lu_group(M, pos, rdiag, P, piv);
+      return lu_group(M, pos, rdiag, P, n, piv);
     }
   }
 
@@ -993,18 +993,21 @@ struct Cell {
   // readlane form needs three. Each element receives the same fused
   // multiply-adds in the same order as column by column.
   // pivot search of one column by value, then position (every special case:
-  // ties, zero columns, non-finite entries)
-  __device__ static __forceinline__ int pivot_exact(double a, int pos, int k, double& amax) {
-    const double key = pos >= k ? fabs(a) : -1.0;
+  // ties, zero columns, non-finite entries). Candidates are the rows at
+  // positions k .. n - 1 (the rows that pad the matrix stay where they are), and
+  // the lane returned always holds one, so that the positions stay a permutation
+  // of the rows: a NaN is not chosen while another candidate compares, and where
+  // none does the row at position k stays.
+  __device__ static __forceinline__ int pivot_exact(double a, int pos, int k, int n, double& amax) {
+    const bool cand = pos >= k && (pos < n || k >= n);
+    const double key = cand ? fabs(a) : -1.0;
     amax = Gp::max(key);
-    const bool tie = key == amax;
-    const unsigned long long bal = __ballot(tie);
-    if (__popcll(bal) == 1) return __ffsll(static_cast<long long>(bal)) - 1;
+    const bool tie = cand && key == amax;
     const int pmin = Gp::min_i(tie ? pos : kBig);
-    return (__ffsll(static_cast<long long>(__ballot(tie && pos == pmin))) - 1) & 63;
+    return Gp::first(pos == (pmin < kBig ? pmin : k));
   }
 
-  __device__ static __forceinline__ int lu_wave(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
+  __device__ static __forceinline__ int lu_wave(double (&M)[NN], int& pos, double& rdiag, double* P, int n, int* piv) {
     unsigned long long zeros = 0;              // columns without a nonzero candidate
     const int i = Gp::lane();
     pos = i < NN ? i : -1;
@@ -1036,7 +1039,7 @@ struct Cell {
           rp = readlane_d(ra, owner);
         } else {
           double amax;
-          owner = __builtin_amdgcn_readfirstlane(pivot_exact(a, pos, k, amax));
+          owner = __builtin_amdgcn_readfirstlane(pivot_exact(a, pos, k, n, amax));
           rp = readlane_d(ra, owner);
           if (amax == 0.0) {
             zeros |= 1ull << k;
@@ -1143,7 +1146,7 @@ struct Cell {
   // multiply-add whose pivot-row element is broadcast along the row by DPP: one
   // LDS round trip a column, where a lane shuffle per element needs two
   // through the LDS crossbar.
-  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, double* P, int* piv) {
+  __device__ static __forceinline__ int lu_group(double (&M)[NN], int& pos, double& rdiag, double* P, int n, int* piv) {
     constexpr int kRow = (NN + 15) & ~15;    // then the reciprocal and the position
     int info = 0;
     const int i = Gp::gl();
@@ -1162,11 +1165,8 @@ struct Cell {
       int owner = __builtin_ctzll(bal);
       bool zero = false;
       if (!__all((bal & (bal - 1)) == 0 && hmax < 0x7ff00000u)) {
-        const double dkey = pos >= k ? fabs(a) : -1.0;
-        const double amax = Gp::max(dkey);
-        const bool tie = dkey == amax;
-        const int pmin = Gp::min_i(tie ? pos : kBig);
-        owner = Gp::first(tie && pos == pmin);
+        double amax;
+        owner = pivot_exact(a, pos, k, n, amax);
         zero = amax == 0.0;
       }
       const bool is_owner = i == owner;
@@ -1330,7 +1330,7 @@ struct Cell {
       }
       j_release(jlock);
     }
-    const int info = lu(M, pos, rdiag, ca.P, nullptr);
+    const int info = lu(M, pos, rdiag, ca.P, n, nullptr);
     ++c.att;
     if (info) {
       c.status = 4;
@@ -1668,7 +1668,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NN > 5
   int piv = 0;
   int pos;
   double rdiag;
-  const int info = C::lu(M, pos, rdiag, S + (G == 64 ? 0 : grp * lu_row_doubles(NN)), &piv);
+  const int info = C::lu(M, pos, rdiag, S + (G == 64 ? 0 : grp * lu_row_doubles(NN)), n, &piv);
   for (int r0 = 0; r0 < n; r0 += step) {
     const int nr = min(step, n - r0);
     const int cnt = G == 64 ? nr * n : mats * n * n;
