@@ -242,21 +242,21 @@ struct Grp {
 // q0*dtheta/d[M], dq/dT) read by the species pass [max(5*nr, 3*NN)]; above 32
 // only the species sums omega, d omega/dT and sum nu q0 dtheta/d[M] [3*NN]
 // that the reaction lanes add into.
-// P is a buffer of the species pass's own (up to 32), and the LU's.
+// P holds the LU's pivot rows, and D (up to 32) takes the adds that the species
+// pass has no element for.
 struct CellArea {
   double* J;
   double* P;
+  double* D;
   double* RB;
   double* C;
   double* gRT;
   double* hRT;
 };
 
-__host__ __device__ constexpr int pbuf_doubles(int nn) { return (nn + 2) & ~1; }
 // The LU's pivot rows of one panel, interleaved (column j's four entries side
 // by side, up to a multiple of 16 columns), sit at the start of the cell's own
-// area above 32 state components (it holds nothing between two right-hand
-// sides), otherwise in P.
+// area, which holds nothing between two right-hand sides.
 constexpr int kPanel = 4;
 __host__ __device__ constexpr int lu_rows_doubles(int nn) { return kPanel * ((nn + 15) & ~15); }
 // one pivot row, its reciprocal and its position (several cells per wave)
@@ -267,10 +267,8 @@ __host__ __device__ constexpr int rbuf_doubles(int nn, int nr) {
   return reaction_major(nn) ? 3 * nn : (5 * nr > 3 * nn ? 5 * nr : 3 * nn);
 }
 __host__ __device__ constexpr int cell_doubles_c(int nn, int nr) {
-  const int vec = 3 * nn + rbuf_doubles(nn, nr);
-  const int pb = lu_rows_doubles(nn) > pbuf_doubles(nn) ? lu_rows_doubles(nn) : pbuf_doubles(nn);
-  const int all = reaction_major(nn) ? (vec > pb ? vec : pb) : ((vec + 1) & ~1) + pb;
-  return (all + 1) & ~1;
+  const int vec = 3 * nn + rbuf_doubles(nn, nr) + (reaction_major(nn) ? 0 : 1);
+  return ((vec > lu_rows_doubles(nn) ? vec : lu_rows_doubles(nn)) + 1) & ~1;
 }
 __host__ __device__ constexpr int j_doubles_c(int nn) { return (nn * nn + 1) & ~1; }
 // Sizes whose waves may share a Jacobian buffer in pairs: one cell per wave,
@@ -285,7 +283,8 @@ __device__ __forceinline__ CellArea cell_area(double* J, double* base, int nr) {
   c.gRT = base + NN;
   c.hRT = base + 2 * NN;
   c.RB = base + 3 * NN;
-  c.P = reaction_major(NN) ? base : base + ((3 * NN + rbuf_doubles(NN, nr) + 1) & ~1);
+  c.P = base;
+  c.D = c.RB + rbuf_doubles(NN, nr);
   return c;
 }
 
@@ -785,9 +784,9 @@ struct Cell {
           wT = wT + nu * dqdT;
           const double af = nu * kfT, ar = nu * krT;
 #pragma unroll
-          for (int j = 0; j < 3; ++j) lds_add(j < nre ? &Jrow[sf[j]] : ca.P, af * dPf[j]);
+          for (int j = 0; j < 3; ++j) lds_add(j < nre ? &Jrow[sf[j]] : ca.D, af * dPf[j]);
 #pragma unroll
-          for (int j = 0; j < 3; ++j) lds_add(j < npr ? &Jrow[sr[j]] : ca.P, -(ar * dPr[j]));
+          for (int j = 0; j < 3; ++j) lds_add(j < npr ? &Jrow[sr[j]] : ca.D, -(ar * dPr[j]));
           const int type = (wc.x >> 28) & 3;
           if (type >= 1) {
             const double ab = nu * q0b;
@@ -1198,6 +1197,7 @@ struct Cell {
         M[j] = fma(-l, row_bcast<(j & 15)>(u[j / 16]), M[j]);
       });
     });
+    wsync();      // the last row is read before the area holds anything else
     // rows to the lanes of their positions
     const int dst = 4 * (Gp::base() + (pos >= 0 ? pos : i));
 #pragma unroll
