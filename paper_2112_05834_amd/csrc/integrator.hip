@@ -411,14 +411,19 @@ struct Cell {
   static constexpr bool kScatter = reaction_major(NN);
 
   // Reactions from the packed records: one lane per reaction, in the order of
-  // the general records and with the same operations per reaction. The
-  // reaction-major assembly adds into the species sums and J (as rx_scatter);
-  // smaller sizes keep the rates in RB for the species pass. The records hold what the general words make every lane decode: LDS offsets
-  // of the species slots (one register serves C, g, h and the sums, by
+  // the general words and with the same operations per reaction, so that both
+  // give the same bits. The reaction-major assembly adds into the species sums
+  // and J (as rx_scatter); smaller sizes keep the rates in RB for the species
+  // pass. The records hold what the general words make every lane decode: LDS
+  // offsets of the species slots (one register serves C, g, h and the sums, by
   // instruction offsets), factors of the mass-action products without selects
   // on the orders, orders as doubles. Products by orders 1 and 2 are exact, so
   // they may be fused. Third slots and factors are handled only in blocks that
-  // have any.
+  // have any; there the B of a side 2A + B, which the record keeps in the third
+  // slot, takes the second species' place in every sum, and the sums are formed
+  // again (kept to this branch, the other blocks pay nothing: with the exchange
+  // ahead of the sums 65536 54-species cells took 141.9 ms, so 140.1, without
+  // it 140.3).
   template <bool JAC>
   __device__ static __forceinline__ void reactions(const MechArgs& A, const MechLds& L, const CellArea& ca, double T,
                                                    double rT, double lnT, double lnRTp, double Ctot) {
@@ -431,7 +436,8 @@ struct Cell {
     const auto at = [&](unsigned off, int arr) { return *reinterpret_cast<const double*>(Cb + off + arr); };
 #pragma nounroll
     for (int r0 = 0; r0 < nr; r0 += G, rec += G) {
-      const double2 k1 = rec[0], k2 = rec[N], n0 = rec[2 * N], n1 = rec[3 * N];
+      const double2 k1 = rec[0], k2 = rec[N], n0 = rec[2 * N];
+      double2 n1 = rec[3 * N];
       const uint4 w0 = reinterpret_cast<const uint4*>(rec)[5 * N];
       const int type = (w0.w >> 8) & 3;
       const bool rev = (w0.w >> 10) & 1;
@@ -439,37 +445,42 @@ struct Cell {
       double2 n2{0.0, 0.0};
       uint4 w1{0, 0, 0, 0};
       if (__any(type != 0) || third) w1 = reinterpret_cast<const uint4*>(rec)[6 * N];
-      const unsigned f0 = w0.x & 0xffff, f1 = w0.x >> 16, p0 = w0.y & 0xffff, p1 = w0.y >> 16;
+      const unsigned f0 = w0.x & 0xffff, p0 = w0.y & 0xffff;
+      unsigned f1 = w0.x >> 16, p1 = w0.y >> 16, f2 = 0, p2 = 0, on = w0.w;   // on: slots with a species
       const double cf0 = at(f0, 0), cp0 = at(p0, 0);
-      double cf1 = at(w0.z & 0xffff, 0), cp1 = at(w0.z >> 16, 0);
+      const double cf1 = at(w0.z & 0xffff, 0), cp1 = at(w0.z >> 16, 0);
       const double lnkf = k1.x + k1.y * lnT - k2.x * rT;
       const double kf = exp(lnkf);
-      double sumg = fma(-n0.x, at(f0, kG), 0.0);
-      sumg = fma(n0.y, at(p0, kG), sumg);
-      sumg = fma(-n1.x, at(f1, kG), sumg);
-      sumg = fma(n1.y, at(p1, kG), sumg);
-      double sumh = 0.0;
-      if (JAC) {
-        sumh = fma(-n0.x, at(f0, kH), 0.0);
-        sumh = fma(n0.y, at(p0, kH), sumh);
-        sumh = fma(-n1.x, at(f1, kH), sumh);
-        sumh = fma(n1.y, at(p1, kH), sumh);
-      }
+      // sum of nu v over slots 0 and 1 of both sides
+      const auto sum01 = [&](int arr) {
+        double v = fma(-n0.x, at(f0, arr), 0.0);
+        v = fma(n0.y, at(p0, arr), v);
+        v = fma(-n1.x, at(f1, arr), v);
+        return fma(n1.y, at(p1, arr), v);
+      };
+      double sumg = sum01(kG), sumh = JAC ? sum01(kH) : 0.0;
       double Pf = cf0 * cf1, Pr = cp0 * cp1;
       double cf2 = 1.0, cp2 = 1.0;
+      bool tf = false, tp = false;      // a side 2A + B: B is the second species, as in the general words
       if (third) {
-        const unsigned f2 = w1.x & 0xffff, p2 = w1.x >> 16;
         n2 = rec[4 * N];
+        f2 = w1.x & 0xffff;
+        p2 = w1.x >> 16;
         cf2 = at(w1.y & 0xffff, 0);
         cp2 = at(w1.y >> 16, 0);
         Pf = Pf * cf2;
         Pr = Pr * cp2;
-        sumg = fma(-n2.x, at(f2, kG), sumg);
-        sumg = fma(n2.y, at(p2, kG), sumg);
-        if (JAC) {
-          sumh = fma(-n2.x, at(f2, kH), sumh);
-          sumh = fma(n2.y, at(p2, kH), sumh);
-        }
+        tf = (on & 6u) == 4u;
+        tp = (on & 48u) == 32u;
+        f1 = tf ? f2 : f1;
+        p1 = tp ? p2 : p1;
+        n1.x = tf ? n2.x : n1.x;
+        n1.y = tp ? n2.y : n1.y;
+        n2.x = tf ? 0.0 : n2.x;
+        n2.y = tp ? 0.0 : n2.y;
+        on ^= (tf ? 6u : 0u) | (tp ? 48u : 0u);
+        sumg = fma(n2.y, at(p2, kG), fma(-n2.x, at(f2, kG), sum01(kG)));
+        if (JAC) sumh = fma(n2.y, at(p2, kH), fma(-n2.x, at(f2, kH), sum01(kH)));
       }
       // kr = kf / Kc with Kc = exp(-sum nu g/RT) (p_atm/RT)^(sum nu)
       double kr = exp(fma(k2.y, lnRTp, lnkf + sumg));
@@ -502,12 +513,12 @@ struct Cell {
       }
       // slots f0 f1 f2 p0 p1 p2: species sums, then J by row and column
       const double nu[6] = {-n0.x, -n1.x, -n2.x, n0.y, n1.y, n2.y};
-      const unsigned off[6] = {f0, f1, w1.x & 0xffff, p0, p1, w1.x >> 16};
+      const unsigned off[6] = {f0, f1, f2, p0, p1, p2};
       const auto each = [&](auto&& fn) {
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
           if (a % 3 == 2 && !third) continue;
-          if (w0.w & (1u << a)) fn(a);
+          if (on & (1u << a)) fn(a);
         }
       };
       each([&](int a) {
@@ -527,10 +538,10 @@ struct Cell {
         dq[2] = dq[5] = 0.0;
         if (third) {
           dq[0] = kfT * (n0.x * cf1 * cf2);
-          dq[1] = kfT * (cf0 * cf2);
+          dq[1] = kfT * (cf0 * (tf ? cf1 : cf2));
           dq[2] = kfT * (cf0 * cf1);
           dq[3] = -(krT * (n0.y * cp1 * cp2));
-          dq[4] = -(krT * (cp0 * cp2));
+          dq[4] = -(krT * (cp0 * (tp ? cp1 : cp2)));
           dq[5] = -(krT * (cp0 * cp1));
         }
         each([&](int a) {
@@ -538,7 +549,7 @@ struct Cell {
 #pragma unroll
           for (int b = 0; b < 6; ++b) {
             if (b % 3 == 2 && !third) continue;
-            if (w0.w & (1u << b)) lds_add(reinterpret_cast<double*>(Jr + off[b]), nu[a] * dq[b]);
+            if (on & (1u << b)) lds_add(reinterpret_cast<double*>(Jr + off[b]), nu[a] * dq[b]);
           }
         });
         if (type >= 1) {
