@@ -17,6 +17,8 @@
 // training is deterministic.
 #include "model.hpp"
 
+#include "bin_direction.hpp"
+
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -536,43 +538,32 @@ __global__ __launch_bounds__(256) void k_bin_count(const float* __restrict__ cos
 }
 
 // Queue offsets: bin 7 first; within a bin, blocks in index order, or (follow)
-// against it where the costs grow with the index: cells of one bin are not all
-// alike, and where the field is sorted or smooth their order then follows the
-// cost too, the longest first. With two waves on a SIMD a long cell takes twice
-// as long while the queue is full, and one that starts late is what the launch
-// waits for (16384 cells by ascending cost, predicted bins: 41.6 ms with the
-// index order inside them, 38.9 against it; queue in index order 40.7).
-// The direction is the sign of the covariance of block and bin, in integers.
+// against it where the costs grow with the index (bins_grow): cells of one bin
+// are not all alike, and where the field is sorted or smooth their order then
+// follows the cost too, the longest first. With two waves on a SIMD a long cell
+// takes twice as long while the queue is full, and one that starts late is what
+// the launch waits for (16384 cells by ascending cost, predicted bins: 41.6 ms
+// with the index order inside them, 38.9 against it; queue in index order 40.7).
+// Up to one block of cells the index order stays.
+static_assert(kDirBins == kBins, "bins");
 __global__ void k_bin_scan(int* __restrict__ cnt, int nblk, int follow) {
-  __shared__ int tot[kBins];
-  __shared__ long long mom[kBins];
+  __shared__ BinSums sums[kBins];
   int* off = cnt + nblk * 9;
   int* flag = off + nblk * kBins;
   const int b = threadIdx.x;
-  if (b < kBins) {
-    int s = 0;
-    long long m = 0;
-    for (int k = 0; k < nblk; ++k) {
-      s += cnt[k * 9 + b];
-      m += static_cast<long long>(cnt[k * 9 + b]) * (2 * k - (nblk - 1));
-    }
-    tot[b] = s;
-    mom[b] = m * (2 * b - (kBins - 1));
-  }
+  if (b < kBins) sums[b] = bin_sums(cnt, 9, nblk, b);
   if (b == kBins) {
     int f = 1;
     for (int k = 0; k < nblk; ++k) f &= cnt[k * 9 + 8];
     flag[0] = f;
   }
   __syncthreads();
-  long long d = 0;
-  for (int h = 0; h < kBins; ++h) d += mom[h];
-  const int step = follow && d > 0 ? -1 : 1;
+  const int step = follow && bins_grow(sums) ? -1 : 1;
   if (b == kBins) flag[1] = step;
   if (b < kBins) {
     int run = 0;
-    for (int h = kBins - 1; h > b; --h) run += tot[h];
-    if (step < 0) run += tot[b] - 1;
+    for (int h = kBins - 1; h > b; --h) run += static_cast<int>(sums[h].cells);
+    if (step < 0) run += static_cast<int>(sums[b].cells) - 1;
     for (int k = 0; k < nblk; ++k) {
       off[k * kBins + b] = run;
       run += step * cnt[k * 9 + b];
