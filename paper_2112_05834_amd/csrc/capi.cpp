@@ -827,12 +827,42 @@ int chem_lu_batch(chem_solver* s, int64_t batch, double* A, int32_t* piv, int32_
     a.ld = s->ld;
     const long long grid = batch < s->wide_slots ? batch : s->wide_slots;
     const size_t lds = chemk::wide_cell_bytes(0, 0, s->ld);
-    HIP_TRY(chemk::launch_lu_wide(static_cast<int>(grid), a, lds, static_cast<hipStream_t>(stream)), "lu launch");
+    HIP_TRY(chemk::launch_lu_wide(static_cast<int>(grid), a, false, lds, static_cast<hipStream_t>(stream)), "lu launch");
     return CHEM_OK;
   }
   const long long per_block = 4LL * sh.cpw;
   const long long grid = (batch + per_block - 1) / per_block;
   HIP_TRY(chemk::launch_lu(sh.v, static_cast<int>(grid), a, static_cast<hipStream_t>(stream)), "lu launch");
+  return CHEM_OK;
+}
+
+// Not in the public header: the LU and the solves of the integration above 64
+// state components on given matrices, so that they can be compared with an exact
+// LU. A [batch][n][n] is replaced by the factors of g I - A in the rows' final
+// order, rows [batch][n] receives the row that each was, info the first zero pivot
+// column + 1, and b, if given, the solutions.
+int chem_check_lu_integration(chem_solver* s, int64_t batch, double g, double* A, int32_t* rows, int32_t* info,
+                              double* b, void* stream) {
+  if (!s || batch < 0 || (batch > 0 && (!A || !rows || !info)))
+    return fail(CHEM_EINVAL, "chem_check_lu_integration: bad argument");
+  if (!s->wide) return fail(CHEM_EUNSUPPORTED, "chem_check_lu_integration: up to 64 state components there is one LU");
+  if (batch == 0) return CHEM_OK;
+  DeviceGuard dg(s->dev);
+  if (int rc = ensure_ws(s)) return rc;
+  chemk::LuArgs a{};
+  a.batch = batch;
+  a.n = s->n;
+  a.A = A;
+  a.piv = rows;
+  a.info = info;
+  a.b = b;
+  a.ws = s->d_ws;
+  a.ws_stride = s->ws_stride;
+  a.ld = s->ld;
+  a.g = g;
+  const long long grid = batch < s->wide_slots ? batch : s->wide_slots;
+  const size_t lds = chemk::wide_cell_bytes(0, 0, s->ld);
+  HIP_TRY(chemk::launch_lu_wide(static_cast<int>(grid), a, true, lds, static_cast<hipStream_t>(stream)), "lu launch");
   return CHEM_OK;
 }
 

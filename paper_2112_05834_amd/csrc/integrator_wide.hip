@@ -1168,6 +1168,13 @@ __device__ __forceinline__ int lu_m(double* M, const double* J, double g, int n,
   return info;
 }
 
+// by the matrix's groups of 64 rows
+__device__ __forceinline__ int lu_by_rows(double* M, const double* J, double g, int n, int ld, const Wide& W) {
+  return ld <= 128   ? lu_m<2>(M, J, g, n, ld, W)
+         : ld <= 192 ? lu_m<3>(M, J, g, n, ld, W)
+                     : lu_m<4>(M, J, g, n, ld, W);
+}
+
 // x = M^-1 b with the factors of lu_w or lu_m; b and x in LDS, distinct.
 // Thread t keeps the element of its own physical row in a register. Forward
 // substitution in blocks of kSB columns (each element receives its terms in
@@ -1406,10 +1413,7 @@ __device__ __forceinline__ void integrate_w(const MechArgs& A, const MechLds& L,
     // M = g I - J, formed by the LU as it first reads each column
     const double g = 1.0 / (TB::gamma * hc);
     __syncthreads();
-    // by the matrix's groups of 64 rows
-    const int info = ld <= 128   ? lu_m<2>(M, J, g, n, ld, W)
-                     : ld <= 192 ? lu_m<3>(M, J, g, n, ld, W)
-                                 : lu_m<4>(M, J, g, n, ld, W);
+    const int info = lu_by_rows(M, J, g, n, ld, W);
     ++att;
     if (info) {
       status = 4;
@@ -1632,6 +1636,39 @@ __global__ void __launch_bounds__(256) k_lu_wide(LuArgs a) {
   }
 }
 
+// The integration's LU and solves on given matrices: factors of g I - A. A and
+// piv come back in the rows' final order, piv with the row of A that each was.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) k_lu_m_wide(LuArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int n = a.n, ld = a.ld;
+  const Wide W = wide_area(reinterpret_cast<double*>(smem), 0, 0, ld);
+  double* J = a.ws + static_cast<long long>(blockIdx.x) * a.ws_stride;
+  double* M = J + static_cast<long long>(n) * ld;
+  const int t = threadIdx.x;
+  const long long nn = static_cast<long long>(n) * n;
+  for (long long m = blockIdx.x; m < a.batch; m += gridDim.x) {
+    for (long long e = t; e < nn; e += kT) {
+      const int i = static_cast<int>(e / n), j = static_cast<int>(e - static_cast<long long>(i) * n);
+      J[j * ld + i] = a.A[m * nn + e];
+    }
+    __syncthreads();
+    const int info = lu_by_rows(M, J, a.g, n, ld, W);
+    for (long long e = t; e < nn; e += kT) {
+      const int j = static_cast<int>(e / n), q = static_cast<int>(e - static_cast<long long>(j) * n);
+      a.A[m * nn + static_cast<long long>(W.pos[q]) * n + j] = M[j * ld + q];
+    }
+    if (t < n) a.piv[m * n + W.pos[t]] = t;
+    if (t == 0) a.info[m] = info;
+    if (a.b) {
+      if (t < n) W.v[t] = a.b[m * n + t];
+      __syncthreads();
+      solve_w(M, n, ld, W, W.v, W.u);
+      if (t < n) a.b[m * n + t] = W.u[t];
+    }
+    __syncthreads();
+  }
+}
+
 }  // namespace
 
 int wide_cell_bytes(int ns, int nr, int ld) { return static_cast<int>(sizeof(double)) * wide_doubles(ns, nr, ld); }
@@ -1674,8 +1711,8 @@ hipError_t launch_eval_wide(int grid, const EvalArgs& a, size_t lds_bytes, hipSt
   return hipLaunchKernel(fn, dim3(grid), dim3(kT), args, lds_bytes, st);
 }
 
-hipError_t launch_lu_wide(int grid, const LuArgs& a, size_t lds_bytes, hipStream_t st) {
-  void* fn = reinterpret_cast<void*>(&k_lu_wide);
+hipError_t launch_lu_wide(int grid, const LuArgs& a, bool integration, size_t lds_bytes, hipStream_t st) {
+  void* fn = integration ? reinterpret_cast<void*>(&k_lu_m_wide) : reinterpret_cast<void*>(&k_lu_wide);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
   if (e != hipSuccess) return e;
   LuArgs copy = a;

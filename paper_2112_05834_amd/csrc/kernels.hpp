@@ -90,6 +90,7 @@ struct LuArgs {
   double* ws;
   long long ws_stride;
   int ld;
+  double g;                     // integration's LU: g I - A is factored
 };
 
 // Kernel variant: state size NN (compiled), lanes per cell G. The
@@ -106,7 +107,8 @@ inline int wide_ld(int n) { return (n + 15) & ~15; }
 int wide_cell_bytes(int ns, int nr, int ld);
 hipError_t launch_integrate_wide(bool persistent, int grid, const IntegrateArgs& a, size_t lds_bytes, hipStream_t st);
 hipError_t launch_eval_wide(int grid, const EvalArgs& a, size_t lds_bytes, hipStream_t st);
-hipError_t launch_lu_wide(int grid, const LuArgs& a, size_t lds_bytes, hipStream_t st);
+// integration: by the LU of the integration, otherwise the batched entry point's
+hipError_t launch_lu_wide(int grid, const LuArgs& a, bool integration, size_t lds_bytes, hipStream_t st);
 int integrate_wide_blocks_per_cu(bool persistent, size_t lds_bytes);
 
 // Which compiled variants exist for a state size n (returns count, fills out).
