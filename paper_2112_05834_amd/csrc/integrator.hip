@@ -1115,7 +1115,11 @@ struct Cell {
 
   // M[c] += sum_k l[k] (x_k of lane N + c of this 16-lane row), k ascending,
   // for NC columns. The leading s_nop covers the wait between a vector write
-  // of x and its use as a DPP operand.
+  // of x and its use as a DPP operand; the outputs are written before all inputs
+  // are read, so they take registers of their own. The compiler does not see a
+  // vector write here, so it adds no wait of its own behind the block: lane reads
+  // of an output need one, and come only after the next panel's pivot search, which
+  // works on the same block's first column.
   template <int NC, int N>
   __device__ static __forceinline__ void rank4(double* m, double x0, double x1, double x2, double x3,
                                                const double (&l)[kPanel]) {
@@ -1123,27 +1127,27 @@ struct Cell {
     if constexpr (NC == 4) {
 #define CHEM_R(X, L) CHEM_F("%0", X, L, "%12") CHEM_F("%1", X, L, "%13") CHEM_F("%2", X, L, "%14") CHEM_F("%3", X, L, "%15")
       asm("s_nop 1\n\t" CHEM_R("%4", "%8") CHEM_R("%5", "%9") CHEM_R("%6", "%10") CHEM_R("%7", "%11")
-          : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3])
+          : "+&v"(m[0]), "+&v"(m[1]), "+&v"(m[2]), "+&v"(m[3])
           : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1),
             "n"(N + 2), "n"(N + 3));
 #undef CHEM_R
     } else if constexpr (NC == 3) {
 #define CHEM_R(X, L) CHEM_F("%0", X, L, "%11") CHEM_F("%1", X, L, "%12") CHEM_F("%2", X, L, "%13")
       asm("s_nop 1\n\t" CHEM_R("%3", "%7") CHEM_R("%4", "%8") CHEM_R("%5", "%9") CHEM_R("%6", "%10")
-          : "+v"(m[0]), "+v"(m[1]), "+v"(m[2])
+          : "+&v"(m[0]), "+&v"(m[1]), "+&v"(m[2])
           : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1),
             "n"(N + 2));
 #undef CHEM_R
     } else if constexpr (NC == 2) {
 #define CHEM_R(X, L) CHEM_F("%0", X, L, "%10") CHEM_F("%1", X, L, "%11")
       asm("s_nop 1\n\t" CHEM_R("%2", "%6") CHEM_R("%3", "%7") CHEM_R("%4", "%8") CHEM_R("%5", "%9")
-          : "+v"(m[0]), "+v"(m[1])
+          : "+&v"(m[0]), "+&v"(m[1])
           : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N), "n"(N + 1));
 #undef CHEM_R
     } else {
 #define CHEM_R(X, L) CHEM_F("%0", X, L, "%9")
       asm("s_nop 1\n\t" CHEM_R("%1", "%5") CHEM_R("%2", "%6") CHEM_R("%3", "%7") CHEM_R("%4", "%8")
-          : "+v"(m[0])
+          : "+&v"(m[0])
           : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "n"(N));
 #undef CHEM_R
     }

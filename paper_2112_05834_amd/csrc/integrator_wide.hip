@@ -838,7 +838,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // t = (lane J of z, by 16-lane rows) * m, rounded (added to zero by the one
-// instruction that takes the broadcast along)
+// instruction that takes the broadcast along). The compiler does not see a vector
+// write in the block and adds no wait behind it: t goes into an ordinary
+// subtraction only, here and in row_sub, never straight into a lane read or a DPP
+// operand.
 template <int J>
 __device__ __forceinline__ double bcast_mul(double z, double m) {
   double t = 0.0;
@@ -848,14 +851,15 @@ __device__ __forceinline__ double bcast_mul(double z, double m) {
   return t;
 }
 
-// x[j] = x[j] - (lane j of z) * m for j = J0 .. 15
+// x[j] = x[j] - (lane j of z) * m for j = J0 .. 15 (the products are written before
+// all inputs are read, so they take registers of their own)
 template <int J0>
 __device__ __forceinline__ void row_sub(double (&x)[kMB], double z, double m) {
 #define CHEM_F(X, J) "v_fmac_f64_dpp " X ", %[z], %[m] row_newbcast:" J " row_mask:0xf bank_mask:0xf\n\t"
   if constexpr (kMB - J0 >= 4) {
     double t[4] = {0.0, 0.0, 0.0, 0.0};
     asm("s_nop 1\n\t" CHEM_F("%0", "%[a]") CHEM_F("%1", "%[b]") CHEM_F("%2", "%[c]") CHEM_F("%3", "%[d]")
-        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3])
+        : "+&v"(t[0]), "+&v"(t[1]), "+&v"(t[2]), "+&v"(t[3])
         : [z] "v"(z), [m] "v"(m), [a] "n"(J0), [b] "n"(J0 + 1), [c] "n"(J0 + 2), [d] "n"(J0 + 3));
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[J0 + i] = x[J0 + i] - t[i];
