@@ -217,8 +217,8 @@ int chem_integrate_steps(chem_solver* s, int32_t n_steps, int64_t n_cells, doubl
  *   n_jac : device [n_cells] int32 or NULL: Jacobian evaluations (analytical,
  *           or one forward-difference Jacobian), one per step start: once at
  *           the start and after every accepted step that the integration
- *           continues from (one formed again after a rejected attempt, where
- *           waves share its buffer, is the same evaluation and not counted);
+ *           continues from (one formed again after a rejected attempt,
+ *           because it was not kept, is the same evaluation and not counted);
  *   n_fev : device [n_cells] int32 or NULL: evaluations of the right-hand
  *           side f: one per step start, the n more that a forward-difference
  *           Jacobian makes, and the stages of every attempt whose LU

@@ -5,9 +5,11 @@
 // of the group owns state component i (0 = T, 1..Ns = Y_1..Y_Ns) and row i of
 // the Rosenbrock matrix M = I/(gamma h) - J, kept in registers. The analytical
 // Jacobian is assembled row-wise in an LDS area, from the mechanism image that
-// every block stages in LDS. The area is the group's own, and keeps J across
-// rejected steps, or (34 to 55 components) shared by two waves, which is what
-// lets two waves run on a SIMD; J is then formed again after a rejected step.
+// every block stages in LDS. The area is the group's own, or (33 to 55
+// components) shared by two waves, which is what lets two waves run on a SIMD.
+// After a rejected step J is formed again above 32 components with the default
+// options, where it goes straight into M, and wherever the area is shared; a
+// group's own area keeps it otherwise.
 //
 // Arithmetic per cell does not depend on G, on the cell's position in the
 // grid or on the schedule: reductions follow one fixed pairing tree over 64
@@ -130,13 +132,6 @@ struct Grp {
   __device__ static __forceinline__ double bcast(double v, int src) {
     if constexpr (G == 64) {
       return readlane_d(v, __builtin_amdgcn_readfirstlane(src));
-    } else {
-      return __shfl(v, base() + src, 64);
-    }
-  }
-  __device__ static __forceinline__ int bcast_i(int v, int src) {
-    if constexpr (G == 64) {
-      return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src));
     } else {
       return __shfl(v, base() + src, 64);
     }
@@ -1718,10 +1713,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NN > 5
 // (integrator_wave.hip), compiled without the machine-level hoisting of loop
 // invariants: in their step loop it moves more 64-bit constants (of log and exp,
 // mostly) into registers than there are, and each is reloaded from scratch at its
-// use, one wait after the other (54 species: 88 spilled registers with it, 21
-// without; 131 cells 16.1 ms with, 15.1 without; 32768 cells 79.7 and 77.0).
+// use, one wait after the other (54 species: 89 spilled registers with it, 24
+// without; 131 cells 16.0 ms with, 15.0 without; 32768 cells 79.6 and 76.7).
 // Variants with several cells per wave have registers to spare and lose by it
-// (9 species, 1024 cells: 5.1 ms with, 5.4 without).
+// (9 species, 1024 cells, four a wave: 5.2 ms with, 5.4 without).
 #define CHEM_VARIANTS(X) \
   X(10, 16)              \
   X(10, 64)              \

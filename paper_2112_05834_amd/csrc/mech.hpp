@@ -45,9 +45,9 @@ struct Packed {
       off_rW;
   int lds_bytes;    // leading part of blob staged in LDS
   int ntroe, neff, nent;
-  // Reaction records of the per-wave kernel above 32 state components: seven
-  // arrays of rec_n 16-byte entries (nr rounded up to 64, absent reactions
-  // without species):
+  // Reaction records of the per-wave kernel (up to 64 state components, 63
+  // species): seven arrays of rec_n 16-byte entries (nr rounded up to 64, absent
+  // reactions without species):
   //   (ln A, b), (Ea/R, sum nu), (order of reactant 0, of product 0), (of 1,
   //   of 1), (of 2, of 2) as doubles; then two of 32-bit words
   //   w0 = slot offsets f0 | f1 << 16, r0 | r1 << 16, second factors ef | er << 16, flags
@@ -56,6 +56,7 @@ struct Packed {
   // kernel keeps a concentration of 1 and zero g and h. A side's mass-action
   // product is C[slot 0] * C[second] * C[third]. Flags: bits 0..5 slot present
   // (f0 f1 f2 r0 r1 r2), 6 a side with three factors, 8..9 type, 10 reversible.
+  // The second species of a side 2A + B is in slot 2; the sums take it second.
   // Empty if a side does not fit (a total order above 3, a species of order 2
   // after another, order 3): such mechanisms use the general records.
   std::vector<uint8_t> rec;
