@@ -940,21 +940,35 @@ struct Cell {
     wsync();
   }
 
-  // Jacobian by forward differences, written row-major into ca.J: one more
-  // right-hand side per integrated component (f0 = f(y) given). Every lane
-  // holds its component of the perturbed state; lane j adds the increment.
-  // Without the bath gas the perturbed state's bath lane is derived again,
-  // so the columns are those of the reduced system, and the bath's row stays
-  // zero.
-  __device__ static void fd_jacobian(const MechArgs& A, const MechLds& L, const CellArea& ca, double p, double y,
-                                     double f0, bool nb) {
+  // one column into the last of M, the others moving up
+  __device__ static __forceinline__ void shift_in(double (&M)[NN], double v) {
+    static_for<NN - 1>([&](auto kc) { M[decltype(kc)::value] = M[decltype(kc)::value + 1]; });
+    M[NN - 1] = v;
+  }
+
+  // Jacobian by forward differences: one more right-hand side per integrated
+  // component (f0 = f(y) given). Every lane holds its component of the
+  // perturbed state; lane j adds the increment. Without the bath gas the
+  // perturbed state's bath lane is derived again, so the columns are those of
+  // the reduced system, and the bath's row stays zero. J is written row-major
+  // into ca.J, or (regs) its columns are shifted into the registers of M, so that
+  // a buffer that two waves share is not held through n right-hand sides:
+  // held, the two ran one after the other (3000 cells, 41 and 55 components: 194
+  // and 540 ms so, 116 and 318 through M; with buffers of their own and one wave
+  // per SIMD 144 and 428). What both ways share stands outside the branches:
+  // stores to M and to ca.J in the two arms of one are merged into stores by
+  // address, and M goes to scratch.
+  __device__ static __forceinline__ void fd_jacobian(const MechArgs& A, const MechLds& L, const CellArea& ca, double p,
+                                                     double y, double f0, bool nb, bool regs, double (&M)[NN]) {
     const int ns = A.ns;
     const int n = nb ? ns : ns + 1;
     const int i = Gp::gl();
-    if (i < NN) {
+    if (!regs && i < NN) {
 #pragma unroll
       for (int j = 0; j < NN; ++j) ca.J[i * NN + j] = 0.0;
     }
+#pragma unroll
+    for (int j = 0; j < NN; ++j) M[j] = 0.0;
 #pragma nounroll
     for (int j = 0; j < n; ++j) {
       const double yj = Gp::bcast(y, j);
@@ -963,7 +977,14 @@ struct Cell {
       double ypert = i == j ? yp : y;
       if (nb) ypert = with_bath(ns, ypert);
       const double fj = rhs<false>(A, L, ca, p, ypert);
-      if (i < NN && !(nb && i == ns)) ca.J[i * NN + j] = (fj - f0) / d;
+      const bool row = i < NN && !(nb && i == ns);
+      const double v = (fj - f0) / d;
+      if constexpr (can_share_j(NN)) shift_in(M, row ? v : 0.0);
+      if (!regs && row) ca.J[i * NN + j] = v;
+    }
+    if constexpr (can_share_j(NN)) {
+#pragma nounroll
+      for (int j = n; j < NN; ++j) shift_in(M, 0.0);
     }
     wsync();
   }
@@ -1319,26 +1340,32 @@ struct Cell {
       c.need = false;
     } else {
       // f and J of the step start. A buffer of the wave's own keeps J
-      // across rejected attempts; a shared one may have been overwritten
-      j_acquire(jlock);
+      // across rejected attempts; a shared one may have been overwritten, and
+      // is not used at all by forward differences
+      const bool regs = GEN && can_share_j(NN) && o.jac_fd && jlock;
+      if (!regs) j_acquire(jlock);
       if (c.need || jlock) {
         if (GEN && o.jac_fd) {
           c.f0 = rhs<false>(A, L, ca, c.p, c.y);
-          fd_jacobian(A, L, ca, c.p, c.y, c.f0, nb);
+          fd_jacobian(A, L, ca, c.p, c.y, c.f0, nb, regs, M);
         } else {
           c.f0 = rhs<true>(A, L, ca, c.p, c.y);
           if (nb) reduce_bath(ca, ns);
         }
         c.need = false;
       }
-      if (i < NN) {
+      if (!regs) {
+        if (i < NN) {
 #pragma unroll
-        for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - ca.J[i * NN + j];
-      } else {
+          for (int j = 0; j < NN; ++j) M[j] = ca.J[i * NN + j];
+        } else {
 #pragma unroll
-        for (int j = 0; j < NN; ++j) M[j] = 0.0;
+          for (int j = 0; j < NN; ++j) M[j] = 0.0;
+        }
+        j_release(jlock);
       }
-      j_release(jlock);
+#pragma unroll
+      for (int j = 0; j < NN; ++j) M[j] = (i == j ? g : 0.0) - M[j];
     }
     const int info = lu(M, pos, rdiag, ca.P, n, nullptr);
     ++c.att;
